@@ -40,31 +40,19 @@ namespace {
 // over the rest. Lane cl of a group returns the sum of row cl >> (LTPR - LG).
 template <int LTPR, int LG>
 __device__ __forceinline__ float kfb_rows_reduce(float* v) {
-    constexpr int TPR = 1 << LTPR;
-    constexpr int G = 1 << LG;
-    const int lane = __lane_id();
-#pragma unroll
-    for (int t = 0; t < LG; ++t) {
-        const int half = G >> (t + 1);
-        const int mask = (TPR >> 1) >> t;
-        const bool hi = (lane & mask) != 0;
-#pragma unroll
-        for (int j = 0; j < half; ++j) {
-            const float send = hi ? v[j] : v[j + half];
-            const float keep = hi ? v[j + half] : v[j];
-            v[j] = keep + kf_xor(send, mask);
-        }
-    }
-    float s = v[0];
-#pragma unroll
-    for (int mask = (TPR >> 1) >> LG; mask >= 1; mask >>= 1) s += kf_xor(s, mask);
-    return s;
+    return kf_rows_reduce_from<(1 << LTPR) / 2, (1 << LG)>(v);
 }
 
-__device__ __forceinline__ kf_f4 kfb_xor4(kf_f4 v, int m) {
-    kf_f4 r;
-    r.x = kf_xor(v.x, m); r.y = kf_xor(v.y, m); r.z = kf_xor(v.z, m); r.w = kf_xor(v.w, m);
-    return r;
+// a(l) + a(l ^ M) for M = TPR, 2 TPR, ..., 32
+template <int M>
+__device__ __forceinline__ kf_f4 kfb_fold4(kf_f4 a) {
+    if constexpr (M < 64) {
+        kf_f4 r;
+        r.x = kf_xor_add<M>(a.x); r.y = kf_xor_add<M>(a.y); r.z = kf_xor_add<M>(a.z); r.w = kf_xor_add<M>(a.w);
+        return kfb_fold4<2 * M>(r);
+    } else {
+        return a;
+    }
 }
 
 // Sum of the column partials of a split instance's row blocks 0 .. nblk - 1
@@ -85,10 +73,7 @@ __device__ __forceinline__ void kfb_colsum(kf_f4* acc, kf_f4* red, Emit emit) {
     const int lane = __lane_id();
     const int wave = threadIdx.x >> 6;
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-#pragma unroll
-        for (int m = TPR; m < 64; m <<= 1) acc[k] += kfb_xor4(acc[k], m);
-    }
+    for (int k = 0; k < K; ++k) acc[k] = kfb_fold4<TPR>(acc[k]);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         __syncthreads();

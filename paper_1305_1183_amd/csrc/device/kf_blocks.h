@@ -153,46 +153,85 @@ __device__ __forceinline__ float kf_dot4(kf_f4 a, kf_f4 b, float acc) {
 }
 
 // ---- B4: cross-lane reductions over the 64-lane wavefront --------------------
-__device__ __forceinline__ float kf_xor(float v, int mask) {
-    const int lane = __lane_id();
-    const int src = (lane ^ mask) << 2;
-    return __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(v)));
+// Exchanges stay in the vector ALU. Halves and quarters of the wave are
+// swapped by v_permlane32_swap / v_permlane16_swap; inside a row of 16 lanes a
+// DPP modifier on the add reads the other lane. A chain of six ds_bpermute
+// exchanges waits for the LDS pipe at every link instead (about 100 cycles
+// each, once per row group). Each lane adds the same pairs as a bpermute
+// butterfly would, so the results do not change by a bit. Measured against the
+// bpermute chain (whole plans): single-pass ATAX 30011 x 1021 85.3 -> 78.3 us,
+// BiCGK n = 1024 9.2 -> 8.3 us, GESUMMV n = 5003 47.4 -> 46.5 us, BiCGK
+// n = 16384 181.4 -> 180.0 us.
+//
+// The values of the two lanes l and l ^ MASK (MASK 32 or 16) as (x, y): of a
+// where bit MASK of l is clear and of b where it is set, the lower lane's first.
+template <int MASK>
+__device__ __forceinline__ kf_f2 kf_swap(float a, float b) {
+    kf_f2 r;
+    if constexpr (MASK == 32) {
+        const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        r.x = __uint_as_float(t[0]); r.y = __uint_as_float(t[1]);
+    } else {
+        const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        r.x = __uint_as_float(t[0]); r.y = __uint_as_float(t[1]);
+    }
+    return r;
+}
+template <int CTRL>
+__device__ __forceinline__ float kf_dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+// v(l ^ MASK) for MASK 8, 4, 2, 1 (inside a row of 16 lanes).
+template <int MASK>
+__device__ __forceinline__ float kf_row_xor(float v) {
+    if constexpr (MASK == 8) return kf_dpp<0x128>(v);               // row_ror:8
+    else if constexpr (MASK == 4) return kf_dpp<0x1b>(kf_dpp<0x141>(v));   // l ^ 7 (row_half_mirror), then ^ 3
+    else if constexpr (MASK == 2) return kf_dpp<0x4e>(v);           // quad_perm:[2,3,0,1]
+    else return kf_dpp<0xb1>(v);                                    // quad_perm:[1,0,3,2]
+}
+// v(l) + v(l ^ MASK)
+template <int MASK>
+__device__ __forceinline__ float kf_xor_add(float v) {
+    if constexpr (MASK >= 16) { const kf_f2 t = kf_swap<MASK>(v, v); return t.x + t.y; }
+    else return v + kf_row_xor<MASK>(v);
+}
+// Butterfly over lane bits MASK, MASK / 2, ..., 1 (MASK 0: nothing).
+template <int MASK>
+__device__ __forceinline__ float kf_butterfly(float v) {
+    if constexpr (MASK > 0) return kf_butterfly<MASK / 2>(kf_xor_add<MASK>(v));
+    else return v;
 }
 // Butterfly: every lane ends with the sum of all 64 lanes (same value in all).
-__device__ __forceinline__ float kf_wave_sum(float v) {
-    v += kf_xor(v, 32);
-    v += kf_xor(v, 16);
-    v += kf_xor(v, 8);
-    v += kf_xor(v, 4);
-    v += kf_xor(v, 2);
-    v += kf_xor(v, 1);
-    return v;
-}
+__device__ __forceinline__ float kf_wave_sum(float v) { return kf_butterfly<32>(v); }
 // Transposing reduction of G = 2^LG row partials held by every lane. Stage t
 // exchanges half of the remaining values with the lane whose bit (5 - t)
 // differs, so after LG stages lane l holds one partial of row l >> (6 - LG);
 // a butterfly over the low 6 - LG bits then completes the sum. G rows cost
 // G - 1 + (6 - LG) exchanges instead of 6 G.
-template <int LG>
-__device__ __forceinline__ float kf_rows_reduce(float* v) {
-    const int lane = __lane_id();
-    constexpr int G = 1 << LG;
-#pragma unroll
-    for (int t = 0; t < LG; ++t) {
-        const int half = G >> (t + 1);
-        const int mask = 32 >> t;
-        const bool hi = (lane & mask) != 0;
+template <int MASK, int G>
+__device__ __forceinline__ float kf_rows_reduce_from(float* v) {
+    if constexpr (G == 1) {
+        return kf_butterfly<MASK>(v[0]);
+    } else {
+        constexpr int half = G / 2;
 #pragma unroll
         for (int j = 0; j < half; ++j) {
-            const float send = hi ? v[j] : v[j + half];
-            const float keep = hi ? v[j + half] : v[j];
-            v[j] = keep + kf_xor(send, mask);
+            if constexpr (MASK >= 16) {
+                const kf_f2 t = kf_swap<MASK>(v[j], v[j + half]);
+                v[j] = t.x + t.y;
+            } else {
+                const bool hi = (__lane_id() & MASK) != 0;
+                const float send = hi ? v[j] : v[j + half];
+                const float keep = hi ? v[j + half] : v[j];
+                v[j] = keep + kf_row_xor<MASK>(send);
+            }
         }
+        return kf_rows_reduce_from<MASK / 2, half>(v);
     }
-    float s = v[0];
-#pragma unroll
-    for (int mask = (32 >> LG); mask >= 1; mask >>= 1) s += kf_xor(s, mask);
-    return s;
+}
+template <int LG>
+__device__ __forceinline__ float kf_rows_reduce(float* v) {
+    return kf_rows_reduce_from<32, (1 << LG)>(v);
 }
 
 // ---- B6: workgroup sum in wave order -----------------------------------------
@@ -275,30 +314,22 @@ __device__ __forceinline__ kf_f4 kf_cs4_value(kf_cs4 a) {
     return r;
 }
 
-// Butterfly over the 64 lanes on pairs: every lane ends with the same pair.
-__device__ __forceinline__ kf_cs kf_wave_sum_cs(kf_cs v) {
-#pragma unroll
-    for (int mask = 32; mask >= 1; mask >>= 1) {
-        kf_cs o;
-        o.s = kf_xor(v.s, mask);
-        o.c = kf_xor(v.c, mask);
-        v = kf_cs_merge(v, o);
-    }
-    return v;
-}
-// The same butterfly within aligned groups of NL lanes (NL a power of two,
-// at most 64): every lane of a group ends with the merge of the group's pairs.
+// Butterfly within aligned groups of NL lanes (NL a power of two, at most 64)
+// on pairs: every lane of a group ends with the merge of the group's pairs.
 template <int NL>
 __device__ __forceinline__ kf_cs kf_group_sum_cs(kf_cs v) {
-#pragma unroll
-    for (int mask = NL / 2; mask >= 1; mask >>= 1) {
-        kf_cs o;
-        o.s = kf_xor(v.s, mask);
-        o.c = kf_xor(v.c, mask);
-        v = kf_cs_merge(v, o);
+    if constexpr (NL == 1) {
+        return v;
+    } else if constexpr (NL >= 32) {
+        const kf_f2 s = kf_swap<NL / 2>(v.s, v.s), c = kf_swap<NL / 2>(v.c, v.c);
+        return kf_group_sum_cs<NL / 2>(kf_cs_merge(kf_cs{s.x, c.x}, kf_cs{s.y, c.y}));
+    } else {
+        const kf_cs o = {kf_row_xor<NL / 2>(v.s), kf_row_xor<NL / 2>(v.c)};
+        return kf_group_sum_cs<NL / 2>(kf_cs_merge(v, o));
     }
-    return v;
 }
+// The same over the whole wave.
+__device__ __forceinline__ kf_cs kf_wave_sum_cs(kf_cs v) { return kf_group_sum_cs<64>(v); }
 // Lane src's value of v (src wave-uniform), as a scalar in every lane.
 __device__ __forceinline__ float kf_lane_bcast(float v, int src) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
