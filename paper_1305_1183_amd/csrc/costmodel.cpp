@@ -18,7 +18,11 @@
 namespace kf {
 hipError_t mlp_gemm(int M, int N, int K, const float* A, long sai, long sak, const float* B, long sbk, long sbj,
                     float* C, long ldc, const float* bias, int relu, const float* mask, long ldm, hipStream_t st);
-hipError_t mlp_colsum(int M, int N, const float* dY, long ld, float* db, hipStream_t st);
+bool mlp_rows_fit(int d, int h);
+hipError_t mlp_rows(int n, int d, int h, int L, const float* P, const float* X, const float* y, float* H, float* dZ,
+                    float* pred, float* dpred, hipStream_t st);
+hipError_t mlp_wgrad(int n, int count, const float* const* A, const float* const* D, float* const* G, const int* in,
+                     const int* out, const float* pred, const float* y, float* loss, hipStream_t st);
 hipError_t mlp_mse(int n, const float* p, const float* y, float* dp, float* loss, hipStream_t st);
 hipError_t mlp_adam(long n, float* p, const float* g, float* m, float* v, float lr, float b1, float b2, float eps,
                     float c1, float c2, hipStream_t st);
@@ -34,9 +38,15 @@ struct kf_mlp {
 
 namespace {
 
-// Workspace: L activation buffers (n x h), prediction and its gradient (n),
-// two gradient buffers (n x h), padded.
-size_t ws_floats(const kf_mlp* m, long n) { return (size_t)(m->L + 2) * n * m->h + 2 * (size_t)n + 64; }
+// Workspace: L activation buffers and L pre-activation gradients (n x h each),
+// the prediction and its gradient (n each), padded. Networks too wide for the
+// block kernel, and callers with a smaller workspace, run layer by layer with
+// two gradient buffers in turn, which needs ws_floats_min.
+size_t ws_floats_min(const kf_mlp* m, long n) { return (size_t)(m->L + 2) * n * m->h + 2 * (size_t)n + 64; }
+size_t ws_floats(const kf_mlp* m, long n) {
+    if (!mlp_rows_fit(m->d, m->h)) return ws_floats_min(m, n);
+    return (size_t)std::max(m->L + 2, 2 * m->L) * n * m->h + 2 * (size_t)n + 64;
+}
 
 #define HIPCHK(x)                                                                     \
     do {                                                                              \
@@ -131,9 +141,13 @@ kf_status kf_mlp_workspace_bytes(const kf_mlp* m, int32_t batch, size_t* bytes) 
 kf_status kf_mlp_forward(const kf_mlp* m, const float* params, const float* X, int32_t n, float* pred, void* ws,
                          size_t ws_bytes, void* stream) {
     if (!m || !params || !X || !pred || !ws || n < 1) return set_error(KF_ERR_ARG, "bad argument");
-    if (ws_bytes < ws_floats(m, n) * sizeof(float)) return set_error(KF_ERR_WORKSPACE, "MLP workspace too small");
+    if (ws_bytes < ws_floats_min(m, n) * sizeof(float)) return set_error(KF_ERR_WORKSPACE, "MLP workspace too small");
     hipStream_t st = (hipStream_t)stream;
     float* w = (float*)ws;
+    if (mlp_rows_fit(m->d, m->h)) {
+        HIPCHK(mlp_rows(n, m->d, m->h, m->L, params, X, nullptr, nullptr, nullptr, pred, nullptr, st));
+        return KF_OK;
+    }
     kf_status s = forward(m, params, X, n, w, st);
     if (s != KF_OK) return s;
     const float* p = w + (size_t)(m->L + 2) * n * m->h;
@@ -144,28 +158,52 @@ kf_status kf_mlp_forward(const kf_mlp* m, const float* params, const float* X, i
 kf_status kf_mlp_loss_grad(const kf_mlp* m, const float* params, const float* X, const float* y, int32_t n,
                            float* grads, float* loss, void* ws, size_t ws_bytes, void* stream) {
     if (!m || !params || !X || !y || !grads || !ws || n < 1) return set_error(KF_ERR_ARG, "bad argument");
-    if (ws_bytes < ws_floats(m, n) * sizeof(float)) return set_error(KF_ERR_WORKSPACE, "MLP workspace too small");
+    if (ws_bytes < ws_floats_min(m, n) * sizeof(float)) return set_error(KF_ERR_WORKSPACE, "MLP workspace too small");
     hipStream_t st = (hipStream_t)stream;
     float* w = (float*)ws;
+    const int h = m->h, L = m->L;
+    auto H = [&](int l) -> const float* { return l == 0 ? X : w + (size_t)(l - 1) * n * h; };  // input of layer l
+    // the block kernel keeps every layer's gradient, so that all weight gradients
+    // come from one launch: 3 launches a step against 5 L + 5
+    if (mlp_rows_fit(m->d, h) && ws_bytes >= ws_floats(m, n) * sizeof(float)) {
+        float* dZ = w + (size_t)L * n * h;
+        float* pred = w + (size_t)2 * L * n * h;
+        float* dpred = pred + n;
+        HIPCHK(mlp_rows(n, m->d, h, L, params, X, y, w, dZ, pred, dpred, st));
+        const float *A[17], *D[17];
+        float* G[17];
+        int in[17], out[17];
+        for (int l = 0; l <= L; ++l) {
+            A[l] = H(l);
+            D[l] = l == L ? dpred : dZ + (size_t)l * n * h;
+            G[l] = grads + m->w_off[l];
+            in[l] = (int)m->in_dim[l];
+            out[l] = (int)m->out_dim[l];
+        }
+        HIPCHK(mlp_wgrad(n, L + 1, A, D, G, in, out, pred, y, loss, st));
+        return KF_OK;
+    }
     kf_status s = forward(m, params, X, n, w, st);
     if (s != KF_OK) return s;
-    const int h = m->h, L = m->L;
     float* pred = w + (size_t)(L + 2) * n * h;
     float* dpred = pred + n;
     float* g0 = w + (size_t)L * n * h;        // two n x h gradient buffers
     float* g1 = g0 + (size_t)n * h;
-    auto H = [&](int l) -> const float* { return l == 0 ? X : w + (size_t)(l - 1) * n * h; };  // input of layer l
     HIPCHK(mlp_mse(n, pred, y, dpred, loss, st));
+    // the bias gradients follow the weights' in `grads`: one launch gives both
+    auto wgrad = [&](int l, const float* D) {
+        const float* A = H(l);
+        float* G = grads + m->w_off[l];
+        const int in = (int)m->in_dim[l], out = (int)m->out_dim[l];
+        return mlp_wgrad(n, 1, &A, &D, &G, &in, &out, nullptr, nullptr, nullptr, st);
+    };
     // output layer: dW = H_L^T dpred, db = sum dpred, dH_L = dpred W^T masked by H_L > 0
-    HIPCHK(mlp_gemm(h, 1, n, H(L), 1, h, dpred, 1, 1, grads + m->w_off[L], 1, nullptr, 0, nullptr, 0, st));
-    HIPCHK(mlp_colsum(n, 1, dpred, 1, grads + m->b_off[L], st));
+    HIPCHK(wgrad(L, dpred));
     HIPCHK(mlp_gemm(n, h, 1, dpred, 1, 1, params + m->w_off[L], 1, 1, g0, h, nullptr, 0, H(L), h, st));
     float* cur = g0;
     float* nxt = g1;
     for (int l = L - 1; l >= 0; --l) {
-        const long in = m->in_dim[l];
-        HIPCHK(mlp_gemm((int)in, h, n, H(l), 1, in, cur, h, 1, grads + m->w_off[l], h, nullptr, 0, nullptr, 0, st));
-        HIPCHK(mlp_colsum(n, h, cur, h, grads + m->b_off[l], st));
+        HIPCHK(wgrad(l, cur));
         if (l > 0) {
             HIPCHK(mlp_gemm(n, h, h, cur, h, 1, params + m->w_off[l], 1, h, nxt, h, nullptr, 0, H(l), h, st));
             float* t = cur;
@@ -225,7 +263,7 @@ namespace {
 
 const int kPredictChunk = 8192;
 
-CmLayout cm_layout(const kf_mlp* m, int64_t rows) {
+CmLayout cm_layout(const kf_mlp* m, int64_t rows, bool least = false) {
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
     CmLayout L{};
     const size_t pb = up((size_t)m->nparams * 4), d = (size_t)m->d, r = (size_t)rows;
@@ -234,7 +272,7 @@ CmLayout cm_layout(const kf_mlp* m, int64_t rows) {
     L.grads = o; o += pb;
     L.mom1 = o; o += pb;
     L.mom2 = o; o += pb;
-    L.ws_floats = ws_floats(m, rows);
+    L.ws_floats = least ? ws_floats_min(m, rows) : ws_floats(m, rows);
     L.ws = o; o += up(L.ws_floats * 4);
     L.x = o; o += up(r * d * 4);
     L.raw = o; o += up(r * d * 4);
@@ -321,7 +359,8 @@ kf_status kf_costmodel_workspace_bytes(const kf_costmodel* cm, int64_t rows, siz
 kf_status kf_costmodel_bind(kf_costmodel* cm, void* mem, size_t bytes, int64_t rows, void* stream) {
     if (!cm || !mem || rows < 1 || rows > ((int64_t)1 << 24)) return set_error(KF_ERR_ARG, "bad argument");
     if ((uintptr_t)mem % 256) return set_error(KF_ERR_ALIGN, "cost-model memory must be 256-byte aligned");
-    const CmLayout L = cm_layout(cm->m, rows);
+    CmLayout L = cm_layout(cm->m, rows);
+    if (bytes < L.total) L = cm_layout(cm->m, rows, true);   // still enough for layer-by-layer steps
     if (bytes < L.total) return set_error(KF_ERR_WORKSPACE, "cost-model memory smaller than kf_costmodel_workspace_bytes");
     if (cm->mem) {   // keep what training did in the memory bound before
         HIPCHK(hipStreamSynchronize((hipStream_t)stream));
