@@ -880,6 +880,24 @@ bool needs_rowres(const Script& s, const std::vector<int>& calls) {
     return false;
 }
 
+// Rows of at most 2048 columns fit one wave: eight teams of one wave each walk
+// rows of their own, with no barrier until their column sums are merged at the
+// end. One workgroup per CU as in the wide geometry, so no more partials; short
+// matrices keep four rows per team. Single-pass ATAX, whole plans: 30011 x 1021
+// 77 us -> 27 us (sixteen teams 28), 20000 x 1500 60 -> 27, 32768 x 256 31 -> 13
+// (four rows per group; one row per group 24), 1024 x 1024 9.3 -> 6.4.
+static RowresGeom rowres_team_geometry(int64_t rows, int64_t cols) {
+    RowresGeom g;
+    g.W = g.WP = 1;
+    g.T = 8;
+    g.KP = (int)((cols + 255) / 256);
+    g.G = std::max(1, 4 / g.KP);
+    const int64_t nb = std::min<int64_t>(256, std::max<int64_t>(1, rows / (g.T * 4)));
+    g.R = (rows + nb - 1) / nb;
+    g.R = (g.R + g.G - 1) / g.G * g.G;   // the staged row vectors cover whole groups
+    return g;
+}
+
 RowresGeom rowres_geometry(int64_t rows, int64_t cols, const MatParams& p) {
     RowresGeom g;
     // enough waves to cover the row 256 columns each (at most 16); G rows per
@@ -946,14 +964,13 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
     for (int v : rowv) push_u(vec_in, v);
 
     RowresGeom geo = rowres_geometry(M, N, p0);
-    const long CW = 256L * geo.KP;
     // Column-indexed vectors live in registers, KP float4 per lane each, or,
     // in kernels that also hold gemtv accumulators in registers, in LDS when
     // all of them fit 128 KiB (one copy per workgroup, zero past N), read at
     // each use: that keeps the loads of a row group in registers without
     // spills. (Column-major GEMVER's three vectors stay in registers: with two
     // of them staged it measured 2% slower.)
-    const size_t vec_lds = (size_t)geo.W * CW * 4;   // bytes of one staged vector
+    const size_t vec_lds = (size_t)geo.W * geo.KP * 1024;   // bytes of one staged vector
     std::vector<int> colv_lds, colv_glob;
     if (!gemtv_calls.empty() && colv.size() * vec_lds <= 128 * 1024) colv_lds = colv;
     // Wider rows (more float4 per lane) or more operands than the registers
@@ -992,10 +1009,22 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
             else colv_glob.push_back(v);
         }
     }
-    const int W = geo.W, WP = geo.WP, KP = geo.KP, G = geo.G;
+    // Narrow rows go to teams of one wave, where registers (two waves per SIMD
+    // leave 256) and LDS (the teams' column sums) hold them.
+    if (auto_geo && N <= 2048) {
+        const RowresGeom tg = rowres_team_geometry(M, N);
+        const size_t lds = 16 + rowv.size() * (size_t)tg.R * 4 + gemtv_calls.size() * (size_t)tg.T * tg.KP * 1024;
+        if (lds <= 160 * 1024 && rowres_pressure(tg.KP, tg.G, nheld, colv.size(), gemtv_calls.size()) <= 160) {
+            geo = tg;
+            colv_lds.clear();
+            colv_glob.clear();
+        }
+    }
+    const int W = geo.W, WP = geo.WP, KP = geo.KP, G = geo.G, T = geo.T;
     int LG = 0;
     while ((1 << LG) < G) ++LG;
-    const int NT = 64 * W;
+    const int NT = 64 * W * T;
+    const long CW = 256L * KP;
     const long R = geo.R;
     const long NB = (M + R - 1) / R;
     const long NP = (N + 3) / 4 * 4;
@@ -1046,11 +1075,15 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
 
     Emitter e;
     e.l(F("constexpr long M = %ldL, N = %ldL, NB = %ldL, NP = %ldL, CW = %ldL, R = %ldL;", M, N, NB, NP, CW, R));
-    e.l(F("constexpr int KP = %d, W = %d, WP = %d, G = %d, LG = %d, NT = %d;", KP, W, WP, G, LG, NT));
+    e.l(F("constexpr int KP = %d, W = %d, WP = %d, G = %d, LG = %d, NT = %d, T = %d;", KP, W, WP, G, LG, NT, T));
     for (int v : mat_in) e.l(F("constexpr long LD%d = %ldL;", v, (long)s.values[v].ld));
     for (int v : mat_out) e.l(F("constexpr long LD%d = %ldL;", v, (long)s.values[v].ld));
-    e.l("const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;");
-    e.l("const long rb = blockIdx.x, r0 = rb * R, r1 = (r0 + R < M) ? r0 + R : M;");
+    e.l("const int tid = threadIdx.x, lane = tid & 63;");
+    // a team's waves split the columns; the teams take row groups in turn
+    e.l(T > 1 ? "constexpr int wave = 0; const int team = __builtin_amdgcn_readfirstlane(tid >> 6);"
+              : "constexpr int team = 0; const int wave = tid >> 6;");
+    // NB row blocks of equal size, at most R rows each
+    e.l("const long rb = blockIdx.x, r0 = rb * M / NB, r1 = (rb + 1) * M / NB;");
     e.l("(void)ws;");
     for (int v : scalars)
         e.l(s.values[v].kind == VK::Const ? F("const float %s = P%d;", scal_name(v).c_str(), v)
@@ -1069,16 +1102,16 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
     }
     for (int v : rowv) {
         e.l(F("__shared__ float rv%d[R];", v));
-        e.l(F("for (long i = tid; i < R; i += NT) rv%d[i] = (r0 + i < M) ? V%d[r0 + i] : 0.f;", v, v));
+        e.l(F("for (long i = tid; i < R; i += NT) rv%d[i] = (r0 + i < r1) ? V%d[r0 + i] : 0.f;", v, v));
     }
     const int ngv = (int)gemv_calls.size();
-    if (ngv) e.l(F("__shared__ float kf_part[2][%d][G][WP];", ngv));
+    if (ngv && T == 1) e.l(F("__shared__ float kf_part[2][%d][G][WP];", ngv));
     for (int c : gemtv_calls) {
         e.l(F("kf_f4 acc%d[KP];", c));
         e.l(F("for (int j = 0; j < KP; ++j) acc%d[j] = kf_zero4();", c));
     }
     e.l("__syncthreads();");
-    e.l("int slot = 0;");
+    if (T == 1) e.l("int slot = 0;");
     auto mexpr = [&](int v) { return produced_in(s, part, kid, v) ? F("m%d[gi]", v) : F("L%d[gi]", v); };
     auto emit_group = [&](bool edge) {
         for (int v : mat_in) e.l(F("kf_f4 L%d[G][KP];", v));
@@ -1121,14 +1154,15 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         // finish the row dots inside the workgroup
         for (int i = 0; i < ngv; ++i) {
             int c = gemv_calls[i];
-            e.l(F("{ const float sw = kf_rows_reduce<LG>(rp%d); if ((lane & ((64 >> LG) - 1)) == 0) kf_part[slot][%d][lane >> (6 - LG)][wave] = sw; }", c, i));
+            if (T > 1) e.l(F("const float fl%d = kf_rows_reduce<LG>(rp%d);", c, c));   // whole rows: lane gi << (6 - LG) holds row gi
+            else e.l(F("{ const float sw = kf_rows_reduce<LG>(rp%d); if ((lane & ((64 >> LG) - 1)) == 0) kf_part[slot][%d][lane >> (6 - LG)][wave] = sw; }", c, i));
         }
-        if (ngv) e.l("__syncthreads();");
+        if (ngv && T == 1) e.l("__syncthreads();");
         // lane l < G WP takes the partial of wave l % WP for row l / WP (zero
         // for l % WP >= W; WP is W rounded up to a power of two); a TwoSum
         // butterfly over each group of WP lanes merges them, in the same fixed
         // order for every row, and lane gi WP then holds row gi's sum
-        for (int i = 0; i < ngv; ++i) {
+        for (int i = 0; i < ngv && T == 1; ++i) {
             int c = gemv_calls[i];
             e.l(F("const float fl%d = kf_cs_value(kf_group_sum_cs<WP>(kf_cs_init((lane < G * WP && (lane & (WP - 1)) < W) ? (&kf_part[slot][%d][0][0])[lane] : 0.f)));", c, i));
         }
@@ -1138,7 +1172,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         e.l("const long row = g0 + gi; const int rl = (int)(row - r0); (void)rl;");
         for (int i = 0; i < ngv; ++i) {
             int c = gemv_calls[i];
-            e.l(F("const float sum%d = kf_lane_bcast(fl%d, gi * WP);", c, c));
+            e.l(F("const float sum%d = kf_lane_bcast(fl%d, %s);", c, c, T > 1 ? "gi << (6 - LG)" : "gi * WP"));
         }
         for (int c : calls) {
             const Call& k = s.calls[c];
@@ -1152,7 +1186,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
                 }
                 e.l(F("const float f%d = %s;", c, val.c_str()));
                 if (must_store(s, part, kid, k.out))
-                    e.l(edge ? F("if (tid == 0 && row < r1) Y%d[row] = f%d;", k.out, c) : F("if (tid == 0) Y%d[row] = f%d;", k.out, c));
+                    e.l(F("if (%s == 0%s) Y%d[row] = f%d;", T > 1 ? "lane" : "tid", edge ? " && row < r1" : "", k.out, c));
                 else e.l(F("(void)f%d;", c));
             } else if (k.op == Op::Gemtv) {
                 std::string xr = produced_in(s, part, kid, k.in[1]) ? F("f%d", s.values[k.in[1]].producer)
@@ -1163,9 +1197,9 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         }
         e.ind--;
         e.l("}");
-        e.l("slot ^= 1;");
+        if (T == 1) e.l("slot ^= 1;");
     };
-    e.l("for (long g0 = r0; g0 < r1; g0 += G) {");
+    e.l("for (long g0 = r0 + team * G; g0 < r1; g0 += T * G) {");
     e.ind++;
     // column vectors read from global memory: an offset the compiler cannot
     // prove constant across groups, so that it does not hoist their loads out
@@ -1185,15 +1219,34 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
     // column results: each wave owns its columns (all gemtv calls in one loop so
     // that a chained y0 is at hand)
     if (!gemtv_calls.empty()) {
-        e.l("for (int j = 0; j < KP; ++j) {");
+        if (T > 1) {
+            // the teams' column sums meet in LDS and are merged in team order, compensated
+            e.l(F("__shared__ kf_f4 kf_red[%d][T][KP * 64];", (int)gemtv_calls.size()));
+            for (size_t i = 0; i < gemtv_calls.size(); ++i)
+                e.l(F("for (int j = 0; j < KP; ++j) kf_red[%zu][team][j * 64 + lane] = acc%d[j];", i, gemtv_calls[i]));
+            e.l("__syncthreads();");
+            e.l("for (int q = tid; q < KP * 64; q += NT) {");
+        } else {
+            e.l("for (int j = 0; j < KP; ++j) {");
+        }
         e.ind++;
-        e.l("const long cc = (long)(cb + 256u * j);");
+        if (T > 1) {
+            for (size_t i = 0; i < gemtv_calls.size(); ++i) {
+                const int c = gemtv_calls[i];
+                e.l(F("kf_cs4 cs%d = kf_cs4_init(kf_red[%zu][0][q]);", c, i));
+                e.l(F("for (int t = 1; t < T; ++t) cs%d = kf_cs4_add(cs%d, kf_red[%zu][t][q]);", c, c, i));
+                e.l(F("const kf_f4 csum%d = kf_cs4_value(cs%d);", c, c));
+            }
+            e.l("const long cc = 4L * q;");
+        } else {
+            e.l("const long cc = (long)(cb + 256u * j);");
+        }
         e.l("if (cc < N) {");
         e.ind++;
         for (int c : gemtv_calls) {
             const Call& k = s.calls[c];
             if (!col_part) {
-                std::string val = F("kf_mul4s(%s, acc%d[j])", scal_name(k.alpha).c_str(), c);
+                std::string val = F("kf_mul4s(%s, %s)", scal_name(k.alpha).c_str(), (T > 1 ? F("csum%d", c) : F("acc%d[j]", c)).c_str());
                 if (k.in[2] >= 0) {
                     std::string y0 = produced_in(s, part, kid, k.in[2]) ? F("g%d", s.values[k.in[2]].producer)
                                                                          : F("kf_ld4_tail(V%d, cc, N)", k.in[2]);
@@ -1203,7 +1256,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
                 if (must_store(s, part, kid, k.out)) e.l(F("kf_st4_tail(Y%d, cc, N, g%d);", k.out, c));
                 else e.l(F("(void)g%d;", c));
             } else {
-                e.l(F("kf_st4(ws + %zuL + rb * NP + cc, acc%d[j]);", ws_off[c], c));
+                e.l(F("kf_st4(ws + %zuL + rb * NP + cc, %s);", ws_off[c], (T > 1 ? F("csum%d", c) : F("acc%d[j]", c)).c_str()));
             }
         }
         e.ind--;
@@ -1263,7 +1316,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
     std::string sigs, fsigs;
     for (size_t i = 0; i < sig.size(); ++i) sigs += (i ? ",\n    " : "    ") + sig[i];
     for (size_t i = 0; i < fsig.size(); ++i) fsigs += (i ? ",\n    " : "    ") + fsig[i];
-    std::string key = F("rowres W%d G%d R%ld M%ld N%ld|", W, G, R, M, N) + sigs + e.o.str() + fsigs + f.o.str();
+    std::string key = F("rowres W%d T%d G%d R%ld M%ld N%ld|", W, T, G, R, M, N) + sigs + e.o.str() + fsigs + f.o.str();
     kc.name = F("kf_row_%016llx", (unsigned long long)fnv1a(key));
     std::ostringstream head;
     head << "extern \"C\" __global__ void __launch_bounds__(" << NT << ") " << kc.name << "(\n" << sigs << ") {\n"
@@ -1279,14 +1332,15 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         kc.launches.push_back(finl);
     }
     kc.source = head.str();
-    kc.lds_bytes = 16 + rowv.size() * (size_t)R * 4 + (size_t)ngv * 2 * G * WP * 4 + colv_lds.size() * (size_t)W * CW * 4;
+    kc.lds_bytes = 16 + rowv.size() * (size_t)R * 4 + (T > 1 ? gemtv_calls.size() * (size_t)T * KP * 1024 : (size_t)ngv * 2 * G * WP * 4) +
+                   colv_lds.size() * (size_t)W * CW * 4;
     // vectors loaded from global memory count too: the loads of a group are
     // all in flight together
     kc.reg_estimate = rowres_pressure(KP, G, nheld, ncv_reg() + colv_glob.size(), gemtv_calls.size());
     kc.over_budget = kc.reg_estimate > budget;
-    kc.params_json = F("{\"schedule\": \"row-resident\", \"waves\": %d, \"group\": %d, \"rows\": %ld, \"kp\": %d, \"row_blocks\": %ld, "
+    kc.params_json = F("{\"schedule\": \"row-resident\", \"waves\": %d, \"teams\": %d, \"group\": %d, \"rows\": %ld, \"kp\": %d, \"row_blocks\": %ld, "
                        "\"register_estimate\": %d, \"over_register_budget\": %s}",
-                       W, G, R, KP, NB, kc.reg_estimate, kc.over_budget ? "true" : "false");
+                       W, T, G, R, KP, NB, kc.reg_estimate, kc.over_budget ? "true" : "false");
     kernel_bytes(s, calls, part, &kc.bytes_read, &kc.bytes_written);
     return kc;
 }

@@ -86,9 +86,9 @@ struct VecParams { int unroll = 0, threads = 0, grid = 0; };
 MatParams default_mat_params(int64_t rows, int64_t cols, const MatParams& req, int e_per_unit = 4);
 int dtype_size(int dtype);
 // Geometry of a row-resident kernel on a rows x cols matrix after defaults:
-// W waves (WP: W rounded up to a power of two), KP float4 per lane per row,
-// G rows per group, R rows per workgroup.
-struct RowresGeom { int W = 0, WP = 0, KP = 0, G = 0; int64_t R = 0; };
+// W waves (WP: W rounded up to a power of two) that share a row, KP float4 per
+// lane per row, G rows per group, R rows per workgroup, T teams of W waves.
+struct RowresGeom { int W = 0, WP = 0, KP = 0, G = 0; int64_t R = 0; int T = 1; };
 RowresGeom rowres_geometry(int64_t rows, int64_t cols, const MatParams& p);
 // Elements per 16-byte unit of the kernel made of `calls` (smallest element size
 // of the matrices it loads).
