@@ -208,7 +208,10 @@ typedef struct kf_compile_opts {
      * (1..16); mat_group: rows per wave step (1, 2, 4, 8, 16); mat_rows: rows
      * per workgroup (multiple of mat_waves*mat_group). vec_unroll: float4 per
      * thread per step (1, 2, 4, 8); vec_threads: 64..1024; vec_grid: max
-     * workgroups (grid-stride beyond). */
+     * workgroups (grid-stride beyond). With no mat_* parameter requested, a
+     * kernel whose reductions are all gemv streams whole rows instead of column
+     * strips ("row-stream" in kf_plan_describe): same strips and bits, no
+     * partial sums in HBM. */
     int32_t mat_k, mat_waves, mat_group, mat_rows;
     int32_t vec_unroll, vec_threads, vec_grid;
     /* BLAS-2 schedule: 0 = column strips x row blocks (mat_k used), 1 = row-
@@ -395,6 +398,8 @@ kf_status kf_time_plan(kf_plan* p, void* stream, int32_t warmup, int32_t reps,
 kf_status kf_time_plan_kernels(kf_plan* p, void* stream, int32_t warmup, int32_t reps, float* us);
 /* The implementation parameters kernel k was generated with, after defaults
  * for its shape were applied (mat_* for BLAS-2 kernels, vec_* for BLAS-1;
+ * row-resident and row-stream kernels report what was requested, 0 for the
+ * library's own geometry;
  * mat_unit as requested, and only for kernels that load a BF16 or FP8
  * matrix). */
 kf_status kf_plan_kernel_params(const kf_plan* p, int32_t k, kf_impl_params* out);

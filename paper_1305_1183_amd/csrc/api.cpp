@@ -625,7 +625,7 @@ kf_status build_plan(const Script& sc, const std::vector<int>& part, const kf_co
                                                  "power of two) must be <= 64");
             }
         } else if (sp.mat) {
-            MatParams q = default_mat_params(sp.a, sp.b, mp, kernel_unit_elems(sc, calls, mp.unit));
+            const MatParams q = kernel_mat_params(sc, calls, mp);
             if (q.rows % (q.waves * q.group)) return set_error(KF_ERR_ARG, "mat_rows must be a multiple of mat_waves * mat_group");
         }
         pk.code = generate_kernel(sc, calls, part, mp, vp);
@@ -1039,8 +1039,8 @@ kf_status kf_plan_kernel_params(const kf_plan* p, int32_t k, kf_impl_params* out
     std::memset(&r, 0, sizeof r);
     if (sp.mat) {
         const bool rowres = pk.mp.sched == 1 || needs_rowres(p->s, pk.code.calls);
-        MatParams q = rowres ? pk.mp
-                             : default_mat_params(sp.a, sp.b, pk.mp, kernel_unit_elems(p->s, pk.code.calls, pk.mp.unit));
+        // row-resident and row-stream kernels report the point they were asked for
+        MatParams q = rowres || pk.code.stream ? pk.mp : kernel_mat_params(p->s, pk.code.calls, pk.mp);
         if (rowres && pk.mp.sched != 1) q.waves = q.group = q.rows = 0;   // strip parameters do not carry over
         r.mat_k = q.k; r.mat_waves = q.waves; r.mat_group = q.group; r.mat_rows = q.rows;
         r.mat_sched = rowres ? 1 : 0;

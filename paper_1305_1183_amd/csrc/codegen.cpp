@@ -19,7 +19,9 @@
 // and a second, small launch adds them in a fixed order and applies the
 // alpha/beta epilogue (Section 3.2.2, final reduction "by extra kernel"):
 // the kernel boundary is the global barrier, so the main pass needs no
-// cross-XCD cache write-back per workgroup.
+// cross-XCD cache write-back per workgroup. Kernels without a gemtv stream
+// whole rows (gen_mat_stream), and kernels in which a gemv feeds a gemtv own
+// whole rows per workgroup (gen_mat_rowres).
 //
 // BLAS-1 kernels (nesting depth 1) stream float4 chunks with a grid-stride
 // loop; dot products reduce per thread, per wave and per workgroup, and the
@@ -281,8 +283,8 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     }
     e.l("const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;");
     e.l("const long sidx = blockIdx.x % S, rb = blockIdx.x / S;");
-    e.l("const long c0 = sidx * C, r0 = rb * R;");
-    e.l("const long r1 = (r0 + R < M) ? r0 + R : M;");
+    // NB row blocks of equal size, at most R rows each
+    e.l("const long c0 = sidx * C, r0 = rb * M / NB, r1 = (rb + 1) * M / NB;");
     e.l("(void)ws;");
     for (int v : scalars) {
         if (s.values[v].kind == VK::Const) e.l(F("const float %s = P%d;", scal_name(v).c_str(), v));
@@ -300,7 +302,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     // row vectors staged in LDS; rows past the end read as zero
     for (int v : rowv) {
         e.l(F("__shared__ float rv%d[R];", v));
-        e.l(F("for (int i = tid; i < R; i += NT) rv%d[i] = (r0 + i < M) ? V%d[r0 + i] : 0.f;", v, v));
+        e.l(F("for (int i = tid; i < R; i += NT) rv%d[i] = (r0 + i < r1) ? V%d[r0 + i] : 0.f;", v, v));
     }
     // cleared accumulators (Algorithm 1, "clear outputs of accumulated reductions")
     for (int c : gemtv_calls) {
@@ -331,9 +333,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         }
     };
 
-    auto emit_loop = [&](bool edge) {
-        e.l("for (long g0 = r0 + (long)wave * G; g0 < r1; g0 += (long)W * G) {");
-        e.ind++;
+    auto emit_loads = [&](bool edge) {
         // loads of every matrix read from HBM (load routines)
         for (int v : mat_in) e.l(F("kf_f4 L%d[G][K];", v));
         e.l("#pragma unroll");
@@ -376,6 +376,8 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         }
         e.ind--;
         e.l("}");
+    };
+    auto emit_compute = [&](bool edge) {
         for (int c : gemv_calls) e.l(F("float rp%d[G];", c));
         e.l("#pragma unroll");
         e.l("for (int gi = 0; gi < G; ++gi) {");
@@ -414,9 +416,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
                 e.l("#pragma unroll");
                 e.l(F("for (int j = 0; j < K; ++j) acc%d[j] = kf_fma4s(xr%d, %s[j], acc%d[j]);", c, c, Min.c_str(), c));
             } else if (k.op == Op::Gemv) {
-                e.l(F("float t%d = 0.f;", c));
-                e.l("#pragma unroll");
-                e.l(F("for (int j = 0; j < K; ++j) t%d = kf_dot4(%s[j], cv%d[j], t%d);", c, Min.c_str(), k.in[1], c));
+                e.l(F("const float t%d = kf_dotk<K>(%s, cv%d);", c, Min.c_str(), k.in[1]));
                 if (qscale >= 0) e.l(F("rp%d[gi] = rv%d[rl] * t%d;", c, qscale, c));
                 else e.l(F("rp%d[gi] = t%d;", c, c));
             }
@@ -442,19 +442,51 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
             e.ind--;
             e.l("}");
         }
-        e.ind--;
-        e.l("}");
     };
-    e.l("const bool edge = (c0 + C > N) || (r0 + R > M);");
-    e.l("if (!edge) {");
+    e.l("const bool cols_in = c0 + C <= N;");
+    // long row ranges: a wave's column sums enter a (sum, error) pair every FL
+    // rows, which keeps the plain FP32 chains short whatever the block's length
+    const int FL = 128;
+    const bool flush = !gemtv_calls.empty() && R > W * FL;
+    if (flush) {
+        for (int c : gemtv_calls) {
+            e.l(F("kf_cs4 tot%d[K];", c));
+            e.l("#pragma unroll");
+            e.l(F("for (int j = 0; j < K; ++j) tot%d[j] = kf_cs4_init(kf_zero4());", c));
+        }
+        e.l(F("for (long h0 = r0; h0 < r1; h0 += W * %d) {", FL));
+        e.ind++;
+        e.l(F("const long h1 = h0 + W * %d < r1 ? h0 + W * %d : r1;", FL, FL));
+    } else {
+        e.l("const long h0 = r0, h1 = r1;");
+    }
+    e.l("for (long g0 = h0 + (long)wave * G; g0 < h1; g0 += (long)W * G) {");
     e.ind++;
-    emit_loop(false);
+    e.l("if (cols_in && g0 + G <= r1) {");
+    e.ind++;
+    emit_loads(false);
+    emit_compute(false);
     e.ind--;
     e.l("} else {");
     e.ind++;
-    emit_loop(true);
+    emit_loads(true);
+    emit_compute(true);
     e.ind--;
     e.l("}");
+    e.ind--;
+    e.l("}");
+    if (flush) {
+        for (int c : gemtv_calls) {
+            e.l("#pragma unroll");
+            e.l(F("for (int j = 0; j < K; ++j) { tot%d[j] = kf_cs4_add(tot%d[j], acc%d[j]); acc%d[j] = kf_zero4(); }", c, c, c, c));
+        }
+        e.ind--;
+        e.l("}");
+        for (int c : gemtv_calls) {
+            e.l("#pragma unroll");
+            e.l(F("for (int j = 0; j < K; ++j) acc%d[j] = kf_cs4_value(tot%d[j]);", c, c));
+        }
+    }
 
     // column reductions: merge the waves in wave order through LDS
     if (!gemtv_calls.empty()) {
@@ -645,6 +677,347 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
                        U, W, G, R, E, S, NB);
     kernel_bytes(s, calls, part, &kc.bytes_read, &kc.bytes_written);
     return kc;
+}
+
+// ============================================================================
+// BLAS-2 kernels without a gemtv: rows streamed by whole waves
+// ============================================================================
+// A kernel whose only reductions are row dots keeps no column accumulators, so
+// nothing ties a workgroup to a column strip: a wave walks a row strip by strip
+// and finishes its dot itself. Against the strip kernels this saves the partial
+// sums in HBM and the finishing launch; against the row-resident schedule, the
+// barrier per row group. The strips, their sums and the compensated merge in
+// strip order are those of the strip kernels of the same shape, so a gemv gives
+// the same bits alone as fused with a gemtv.
+//
+// U strips are in flight per row and step. Where whole rows would leave the chip
+// short of waves, CWV waves share a row (strips cw, cw + CWV, ... in steps); the
+// strip sums then meet in LDS and one lane per row merges them.
+struct StreamGeom { int W, G, U, CWV; };
+static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E, int K);
+
+static bool is_stream(const Script& s, const std::vector<int>& calls, const MatParams& p) {
+    if (!library_geometry(p)) return false;
+    std::set<int> mats, cols;
+    bool gemv = false;
+    for (int c : calls) {
+        const Call& k = s.calls[c];
+        if (k.op == Op::Gemtv) return false;
+        if (k.op == Op::Gemv) gemv = true;
+        if (s.values[k.in[0]].producer < 0 || std::find(calls.begin(), calls.end(), s.values[k.in[0]].producer) == calls.end())
+            mats.insert(k.in[0]);
+        cols.insert(k.op == Op::Gemv ? k.in[1] : k.in[2]);
+    }
+    // eight float4 of every row and column vector are in flight per lane: more
+    // operands than this would spill
+    return gemv && 32 * (mats.size() + cols.size()) <= 192;
+}
+
+static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls, const std::vector<int>& part,
+                                 const MatParams& p) {
+    KernelCode kc;
+    kc.mat = kc.stream = true;
+    kc.calls = calls;
+    const int kid = part[calls[0]];
+    const Space sp = call_space(s, calls[0]);
+    const long M = (long)sp.a, N = (long)sp.b;
+    const int E = kernel_unit_elems(s, calls, p.unit), EG = E / 4;
+    // K float4 groups per lane and strip, as in the strip kernels
+    const int KU = p.k, K = KU * EG;
+
+    std::vector<int> mat_in, mat_out, colv, rowv, vec_in, vec_out, gemv_calls, scalars;
+    auto push_u = [](std::vector<int>& v, int x) {
+        if (std::find(v.begin(), v.end(), x) == v.end()) v.push_back(x);
+    };
+    for (int c : calls) {
+        const Call& k = s.calls[c];
+        if (!produced_in(s, part, kid, k.in[0])) push_u(mat_in, k.in[0]);
+        if (k.op == Op::Ger) {
+            push_u(rowv, k.in[1]);
+            push_u(colv, k.in[2]);
+            if (must_store(s, part, kid, k.out)) push_u(mat_out, k.out);
+        } else {
+            push_u(colv, k.in[1]);
+            gemv_calls.push_back(c);
+            if (k.in[2] >= 0 && !produced_in(s, part, kid, k.in[2])) push_u(vec_in, k.in[2]);
+            if (must_store(s, part, kid, k.out)) push_u(vec_out, k.out);
+        }
+    }
+    for (int v : mat_in)
+        if (s.values[v].scale >= 0) push_u(rowv, s.values[v].scale);
+    for (int v : colv) push_u(vec_in, v);
+    for (int v : rowv) push_u(vec_in, v);
+    StreamGeom geo = stream_geometry(M, N, E, KU);
+    if (gemv_calls.size() * (size_t)(geo.W / geo.CWV) * geo.G * ((N + 64L * E * KU - 1) / (64L * E * KU)) * 4 > 32 * 1024) geo.CWV = 1;
+    const int W = geo.W, G = geo.G, U = geo.U, CWV = geo.CWV, T = W / CWV, NT = 64 * W;
+    const long S = (N + 64L * E * KU - 1) / (64L * E * KU);
+    int LGU = 0;
+    while ((1 << LGU) < G * U) ++LGU;
+    const bool off32 = N < (1L << 28);   // byte offsets inside a row fit 32 bits
+
+    std::vector<std::string> sig;
+    Launch mainl;
+    for (int v : mat_in) {
+        mainl.args.push_back({ArgKind::MatIn, v});
+        sig.push_back(s.values[v].dtype == KF_F32 ? F("const float* __restrict__ M%d", v) : F("const unsigned char* __restrict__ M%d", v));
+    }
+    for (int v : mat_out) { mainl.args.push_back({ArgKind::MatOut, v}); sig.push_back(F("float* __restrict__ O%d", v)); }
+    for (int v : vec_in) { mainl.args.push_back({ArgKind::VecIn, v}); sig.push_back(F("const float* __restrict__ V%d", v)); }
+    for (int v : vec_out) { mainl.args.push_back({ArgKind::VecOut, v}); sig.push_back(F("float* __restrict__ Y%d", v)); }
+    std::vector<KArg> sargs;
+    for (int c : calls) {
+        add_scalar_args(s, s.calls[c].alpha, &sargs, &scalars);
+        if (s.calls[c].in[2] >= 0 && s.calls[c].op != Op::Ger) add_scalar_args(s, s.calls[c].beta, &sargs, &scalars);
+    }
+    for (auto& a : sargs) {
+        mainl.args.push_back(a);
+        sig.push_back(a.kind == ArgKind::ConstScalar ? F("float P%d", a.value) : F("const float* __restrict__ P%d", a.value));
+    }
+    if (p.dyn) {
+        mainl.args.push_back({ArgKind::ShapeM, -1});
+        mainl.args.push_back({ArgKind::ShapeN, -1});
+        sig.push_back("long M_");
+        sig.push_back("long N_");
+        for (int v : mat_in) { mainl.args.push_back({ArgKind::MatLd, v}); sig.push_back(F("long LD%d", v)); }
+        for (int v : mat_out) { mainl.args.push_back({ArgKind::MatLd, v}); sig.push_back(F("long LD%d", v)); }
+    }
+
+    Emitter e;
+    e.l(F("constexpr int W = %d, G = %d, U = %d, LGU = %d, CWV = %d, T = %d, E = %d, EG = %d, K = %d;", W, G, U, LGU, CWV, T, E, EG, K));
+    if (p.dyn) {
+        e.l(F("constexpr long C = %dL, SMAX = %ldL; const long M = M_, N = N_, S = (N + C - 1) / C;", 64 * E * KU, S));
+    } else {
+        e.l(F("constexpr long M = %ldL, N = %ldL, C = %dL, S = %ldL, SMAX = S;", M, N, 64 * E * KU, S));
+        for (int v : mat_in) e.l(F("constexpr long LD%d = %ldL;", v, (long)s.values[v].ld));
+        for (int v : mat_out) e.l(F("constexpr long LD%d = %ldL;", v, (long)s.values[v].ld));
+    }
+    // whole strips, and the start of a row's last unit
+    e.l("const long SF = N / C, clast = (N - 1) / E * E;");
+    e.l("(void)clast;");
+    e.l("const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));");
+    e.l("const int team = wave / CWV, cw = wave % CWV;");
+    e.l("const long g0 = ((long)blockIdx.x * T + team) * G;");
+    for (int v : scalars)
+        e.l(s.values[v].kind == VK::Const ? F("const float %s = P%d;", scal_name(v).c_str(), v)
+                                          : F("const float %s = *P%d;", scal_name(v).c_str(), v));
+    // rows past the end read the last row; their sums are not stored
+    for (int v : mat_in) e.l(F("const %s* A%d[G];", s.values[v].dtype == KF_F32 ? "float" : "unsigned char", v));
+    for (int v : rowv) e.l(F("float rv%d[G];", v));
+    e.l("#pragma unroll");
+    e.l("for (int gi = 0; gi < G; ++gi) {");
+    e.ind++;
+    e.l("const long row = g0 + gi < M ? g0 + gi : M - 1;");
+    for (int v : mat_in) e.l(F("A%d[gi] = M%d + row * LD%d * %d;", v, v, v, s.values[v].dtype == KF_F32 ? 1 : dtype_size(s.values[v].dtype)));
+    for (int v : rowv) e.l(F("rv%d[gi] = V%d[row];", v, v));
+    e.ind--;
+    e.l("}");
+    const int ngv = (int)gemv_calls.size();
+    if (CWV > 1) {
+        e.l(F("__shared__ float kf_part[%d][T][G][SMAX];", ngv));
+    } else {
+        for (int c : gemv_calls) {
+            e.l(F("kf_cs ac%d[G];", c));
+            e.l("#pragma unroll");
+            e.l(F("for (int gi = 0; gi < G; ++gi) ac%d[gi] = kf_cs_init(0.f);", c));
+        }
+    }
+    const char* off = off32 ? "unsigned" : "long";
+    auto emit_step = [&](bool edge) {
+        // loads of the step: every row's units, then the column vectors
+        for (int v : colv) e.l(F("kf_f4 cv%d[U][K];", v));
+        for (int v : mat_in) e.l(F("kf_f4 L%d[G][U][K];", v));
+        e.l("#pragma unroll");
+        e.l("for (int u = 0; u < U; ++u)");
+        e.l("#pragma unroll");
+        e.l("for (int j = 0; j < K; j += EG) {");
+        e.ind++;
+        e.l(F("const %s col = (%s)((c + u * CWV) * C + ((j / EG) * 64 + lane) * E);", off, off));
+        if (edge) e.l(F("const %s cl = (long)col < clast ? col : (%s)clast;", off, off));
+        for (int v : mat_in) {
+            const int dt = s.values[v].dtype, es = dtype_size(dt);
+            const char* at = edge ? "cl" : "col";
+            e.l("#pragma unroll");
+            e.l("for (int gi = 0; gi < G; ++gi) {");
+            e.ind++;
+            if (dt == KF_F32) {
+                // EG groups of an FP32 matrix beside a quantised one
+                e.l("#pragma unroll");
+                e.l(F("for (int q = 0; q < EG; ++q) L%d[gi][u][j + q] = kf_ld4_nt_off(A%d[gi], %s%s);", v, v, at,
+                      edge ? " + ((long)cl + 4 * q < N ? 4 * q : 0)" : " + 4 * q"));
+            } else if (E == 4) {
+                e.l(F("L%d[gi][u][j] = %s(A%d[gi] + %s * %d);", v, dt == KF_BF16 ? "kf_ld4_bf16_nt" : "kf_ld4_fp8_nt", v, at, es));
+            } else {
+                const int per = 16 / es, EQ = per / 4;
+                for (int h = 0; h < E / per; ++h)
+                    e.l(F("%s(kf_ldu_nt(A%d[gi] + (%s%s) * %d), &L%d[gi][u][j + %d]);", dt == KF_BF16 ? "kf_dec_bf16" : "kf_dec_fp8", v, at,
+                          edge ? F(" + ((long)cl + %d < N ? %d : 0)", h * per, h * per).c_str() : F(" + %d", h * per).c_str(), es, v, h * EQ));
+            }
+            if (edge) {
+                e.l("#pragma unroll");
+                e.l(F("for (int q = 0; q < EG; ++q) L%d[gi][u][j + q] = kf_mask4(L%d[gi][u][j + q], (long)col + 4 * q, N);", v, v));
+            }
+            e.ind--;
+            e.l("}");
+        }
+        for (int v : colv) {
+            e.l("#pragma unroll");
+            e.l(edge ? F("for (int q = 0; q < EG; ++q) cv%d[u][j + q] = kf_ld4_tail(V%d, (long)col + 4 * q, N);", v, v)
+                     : F("for (int q = 0; q < EG; ++q) cv%d[u][j + q] = kf_ld4_off(V%d, col + 4 * q);", v, v));
+        }
+        e.ind--;
+        e.l("}");
+        for (int c : gemv_calls) e.l(F("float t%d[G * U];", c));
+        e.l("#pragma unroll");
+        e.l("for (int gi = 0; gi < G; ++gi)");
+        e.l("#pragma unroll");
+        e.l("for (int u = 0; u < U; ++u) {");
+        e.ind++;
+        auto mexpr = [&](int v) { return produced_in(s, part, kid, v) ? F("m%d", v) : F("L%d[gi][u]", v); };
+        for (int c : calls) {
+            const Call& k = s.calls[c];
+            std::string Min = mexpr(k.in[0]);
+            const int qs = s.values[k.in[0]].scale;
+            if (k.op == Op::Ger) {
+                e.l(F("const float cu%d = %s * rv%d[gi];", c, scal_name(k.alpha).c_str(), k.in[1]));
+                e.l(F("kf_f4 m%d[K];", k.out));
+                e.l("#pragma unroll");
+                e.l(F("for (int j = 0; j < K; ++j) m%d[j] = kf_fma4s(cu%d, cv%d[u][j], %s);", k.out, c, k.in[2],
+                      qs >= 0 ? F("kf_mul4s(rv%d[gi], %s[j])", qs, Min.c_str()).c_str() : F("%s[j]", Min.c_str()).c_str()));
+                if (must_store(s, part, kid, k.out)) {
+                    e.l("if (g0 + gi < M) {");
+                    e.l("#pragma unroll");
+                    e.l("for (int j = 0; j < K; ++j) {");
+                    e.l("  const long col = (c + u * CWV) * C + ((j / EG) * 64 + lane) * E + 4 * (j % EG);");
+                    if (edge) e.l(F("  kf_stm_edge(O%d + (g0 + gi) * LD%d, col, N, m%d[j]);", k.out, k.out, k.out));
+                    else e.l(F("  kf_st4_nt(O%d + (g0 + gi) * LD%d + col, m%d[j]);", k.out, k.out, k.out));
+                    e.l("} }");
+                }
+            } else {
+                e.l(F("const float d%d = kf_dotk<K>(%s, cv%d[u]);", c, Min.c_str(), k.in[1]));
+                if (qs >= 0) e.l(F("t%d[gi * U + u] = rv%d[gi] * d%d;", c, qs, c));
+                else e.l(F("t%d[gi * U + u] = d%d;", c, c));
+            }
+        }
+        e.ind--;
+        e.l("}");
+        // strip sums: lane group i of 64 / (G U) lanes gets that of row i / U, strip c + (i % U) CWV
+        for (int i = 0; i < ngv; ++i) {
+            const int c = gemv_calls[i];
+            e.l(F("const float ss%d = kf_rows_reduce<LGU>(t%d);", c, c));
+            if (CWV > 1) {
+                e.l("{ const int i = lane >> (6 - LGU); const long si = c + (i % U) * CWV;");
+                e.l(F("  if ((lane & ((64 >> LGU) - 1)) == 0%s) kf_part[%d][team][i / U][si] = ss%d; }", edge ? " && si < S" : "", i, c));
+            } else {
+                e.l("#pragma unroll");
+                e.l("for (int gi = 0; gi < G; ++gi)");
+                e.l("#pragma unroll");
+                e.l(F("for (int u = 0; u < U; ++u)%s ac%d[gi] = kf_cs_add(ac%d[gi], kf_lane_bcast(ss%d, (gi * U + u) << (6 - LGU)));",
+                      edge ? " if (c + u < S)" : "", c, c, c));
+            }
+        }
+    };
+    e.l("for (long c = cw; c < S; c += U * CWV) {");
+    e.ind++;
+    e.l("if (c + (U - 1) * CWV < SF) {");
+    e.ind++;
+    emit_step(false);
+    e.ind--;
+    e.l("} else {");
+    e.ind++;
+    emit_step(true);
+    e.ind--;
+    e.l("}");
+    e.ind--;
+    e.l("}");
+    // the row's sum in lane gi of the wave (of the first wave, where waves share rows)
+    if (CWV > 1) {
+        e.l("__syncthreads();");
+        e.l("if (cw != 0) return;");
+    }
+    e.l("const long row = g0 + lane;");
+    for (int i = 0; i < ngv; ++i) {
+        const int c = gemv_calls[i];
+        if (CWV > 1) {
+            e.l(F("float sum%d = 0.f;", c));
+            e.l("if (lane < G) {");
+            e.l(F("  kf_cs t = kf_cs_init(kf_part[%d][team][lane][0]);", i));
+            e.l(F("  for (long si = 1; si < S; ++si) t = kf_cs_add(t, kf_part[%d][team][lane][si]);", i));
+            e.l(F("  sum%d = kf_cs_value(t);", c));
+            e.l("}");
+        } else {
+            e.l(F("float sum%d = kf_cs_value(ac%d[0]);", c, c));
+            e.l("#pragma unroll");
+            e.l(F("for (int gi = 1; gi < G; ++gi) sum%d = lane == gi ? kf_cs_value(ac%d[gi]) : sum%d;", c, c, c));
+        }
+    }
+    e.l("if (lane < G && row < M) {");
+    e.ind++;
+    for (int c : gemv_calls) {
+        const Call& k = s.calls[c];
+        std::string val = F("%s * sum%d", scal_name(k.alpha).c_str(), c);
+        if (k.in[2] >= 0) {
+            std::string y0 = produced_in(s, part, kid, k.in[2]) ? F("f%d", s.values[k.in[2]].producer) : F("V%d[row]", k.in[2]);
+            val = F("__builtin_fmaf(%s, %s, %s)", scal_name(k.beta).c_str(), y0.c_str(), val.c_str());
+        }
+        e.l(F("const float f%d = %s;", c, val.c_str()));
+        if (must_store(s, part, kid, k.out)) e.l(F("Y%d[row] = f%d;", k.out, c));
+        else e.l(F("(void)f%d;", c));
+    }
+    e.ind--;
+    e.l("}");
+
+    std::string sigs;
+    for (size_t i = 0; i < sig.size(); ++i) sigs += (i ? ",\n    " : "    ") + sig[i];
+    const std::string body = e.o.str();
+    kc.name = F("kf_str_%016llx", (unsigned long long)fnv1a(F("stream M%ld N%ld%s|", M, N, p.dyn ? " dyn" : "") + sigs + body));
+    kc.source = F("extern \"C\" __global__ void __launch_bounds__(%d) ", NT) + kc.name + "(\n" + sigs + ") {\n" + body + "}\n";
+    mainl.name = kc.name;
+    mainl.grid = (int)((M + T * G - 1) / (T * G));
+    mainl.block = NT;
+    if (p.dyn) {
+        mainl.dyn_grid = 1;
+        mainl.dyn_c = 1L << 40;   // one strip
+        mainl.dyn_r = T * G;
+    }
+    kc.launches.push_back(mainl);
+    kc.lds_bytes = 16 + (CWV > 1 ? gemv_calls.size() * (size_t)T * G * S * 4 : 0);
+    kc.params_json = F("{\"schedule\": \"row-stream\", \"k\": %d, \"waves\": %d, \"group\": %d, \"rows\": %d, \"unroll\": %d, "
+                       "\"column_waves\": %d, \"unit_elems\": %d, \"strips\": %ld}",
+                       KU, W, G, T * G, U, CWV, E, S);
+    kernel_bytes(s, calls, part, &kc.bytes_read, &kc.bytes_written);
+    return kc;
+}
+
+// Sharing a row between waves pays on long rows (fewer rows open at once: GESUMMV
+// n = 16384 302 us with four waves a row, 355 with one) as long as its steps
+// are full; short matrices share rows to have waves at all (512 x 16384: 12 us
+// with four waves a row, 40 with one). Elsewhere a wave per row is best: n = 5003
+// 31 us (the strip kernel and its finishing launch 47), n = 10007 117 us. 16-byte
+// units of BF16 and FP8 read two to four times their own bytes of x, which two
+// or four rows share (gemv of FP8 16384 x 16384: 52 us with four rows, 66 with
+// two).
+static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E, int K) {
+    StreamGeom g{4, 1, 1, 1};
+    const int64_t ch = (cols + 64 * E * K - 1) / (64 * E * K);   // strips of a row
+    int64_t pch = 1;
+    while (pch < ch) pch *= 2;
+    const int full = std::max(1, 8 / K);   // strips in flight per wave: eight float4 per row and lane
+    if (ch <= 4096 && (rows < 1024 || cols >= 8192)) {
+        g.CWV = (int)std::min<int64_t>(4, pch);
+        while (rows >= 1024 && g.CWV > 1) {
+            const int64_t step = (int64_t)full * g.CWV;
+            if (100 * ch >= 85 * ((ch + step - 1) / step * step)) break;
+            g.CWV /= 2;
+        }
+    }
+    if (E > 4) {
+        g.U = K > 1 || ch == 1 ? 1 : 2;
+        g.G = rows >= 1024 ? (ch >= 16 ? 4 : 2) : 1;
+        return g;
+    }
+    g.U = (int)std::min<int64_t>(full, std::max<int64_t>(1, pch / g.CWV));
+    if (g.U * K == 1 && g.CWV == 1 && rows >= 4096) g.G = 4;   // rows of at most 256 columns
+    return g;
 }
 
 // ============================================================================
@@ -1012,7 +1385,8 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
     // Narrow rows go to teams of one wave, where registers (two waves per SIMD
     // leave 256) and LDS (the teams' column sums) hold them.
     if (auto_geo && N <= 2048) {
-        const RowresGeom tg = rowres_team_geometry(M, N);
+        RowresGeom tg = rowres_team_geometry(M, N);
+        tg.R = std::max(tg.R, (rowres_geometry(M, N, p0).R + tg.G - 1) / tg.G * tg.G);   // never more partials than the wide geometry
         const size_t lds = 16 + rowv.size() * (size_t)tg.R * 4 + gemtv_calls.size() * (size_t)tg.T * tg.KP * 1024;
         if (lds <= 160 * 1024 && rowres_pressure(tg.KP, tg.G, nheld, colv.size(), gemtv_calls.size()) <= 160) {
             geo = tg;
@@ -1373,9 +1747,9 @@ KernelCode generate_kernel(const Script& s, const std::vector<int>& calls,
         kc = gen_mat_rowres(s, calls, part, q);
     } else {
         if (sp.mat) {
-            MatParams q = default_mat_params(sp.a, sp.b, mp, kernel_unit_elems(s, calls, mp.unit));
+            MatParams q = kernel_mat_params(s, calls, mp);
             q.dyn = mp.dyn;
-            kc = gen_mat(s, calls, part, q);
+            kc = is_stream(s, calls, mp) ? gen_mat_stream(s, calls, part, q) : gen_mat(s, calls, part, q);
         } else {
             kc = gen_vec(s, calls, part, default_vec_params(sp.a, vp));
         }
@@ -1646,7 +2020,7 @@ void kernel_features(const Script& s, const KernelCode& kc, const std::vector<in
     f[14] = (float)vi;
     f[15] = (float)vo;
     if (sp.mat) {
-        MatParams p = default_mat_params(sp.a, sp.b, mp);
+        MatParams p = default_mat_params(sp.a, sp.b, mp);   // the point as the model knows it
         f[16] = (float)p.k;
         f[17] = (float)p.waves;
         f[18] = lg2(p.group);

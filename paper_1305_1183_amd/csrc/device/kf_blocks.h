@@ -36,6 +36,14 @@ __device__ __forceinline__ kf_f4 kf_ld4_nt_at(const float* base, unsigned off) {
 __device__ __forceinline__ void kf_st4_nt_at(float* base, unsigned off, kf_f4 v) {
     __builtin_nontemporal_store(v, reinterpret_cast<kf_f4*>(reinterpret_cast<char*>(base) + 4u * off));
 }
+// The same at an element offset of either width (a 32-bit byte offset where the
+// row allows it).
+__device__ __forceinline__ kf_f4 kf_ld4_nt_off(const float* base, unsigned off) { return kf_ld4_nt_at(base, off); }
+__device__ __forceinline__ kf_f4 kf_ld4_nt_off(const float* base, long off) { return kf_ld4_nt(base + off); }
+__device__ __forceinline__ kf_f4 kf_ld4_off(const float* base, unsigned off) {
+    return *reinterpret_cast<const kf_f4*>(reinterpret_cast<const char*>(base) + 4u * off);
+}
+__device__ __forceinline__ kf_f4 kf_ld4_off(const float* base, long off) { return kf_ld4(base + off); }
 __device__ __forceinline__ kf_f4 kf_zero4() { kf_f4 z = {0.f, 0.f, 0.f, 0.f}; return z; }
 
 // Vector entries col..col+3, entries at index >= n read as zero (the vector
@@ -150,6 +158,14 @@ __device__ __forceinline__ float kf_dot4(kf_f4 a, kf_f4 b, float acc) {
     acc = __builtin_fmaf(a.z, b.z, acc);
     acc = __builtin_fmaf(a.w, b.w, acc);
     return acc;
+}
+
+// Sum over K float4 pairs: the pairs' own sums, added pairwise, so that wider
+// strips do not lengthen the FMA chain.
+template <int K>
+__device__ __forceinline__ float kf_dotk(const kf_f4* a, const kf_f4* b) {
+    if constexpr (K == 1) return kf_dot4(a[0], b[0], 0.f);
+    else return kf_dotk<K / 2>(a, b) + kf_dotk<K - K / 2>(a + K / 2, b + K / 2);
 }
 
 // ---- B4: cross-lane reductions over the 64-lane wavefront --------------------

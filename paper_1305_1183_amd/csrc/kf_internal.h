@@ -84,6 +84,11 @@ struct VecParams { int unroll = 0, threads = 0, grid = 0; };
 // e_per_unit: matrix elements per 16-byte load unit of the kernel (4 for FP32,
 // 8 with a BF16 matrix, 16 with an FP8 matrix).
 MatParams default_mat_params(int64_t rows, int64_t cols, const MatParams& req, int e_per_unit = 4);
+// Nothing requested: the kernel takes the library's own geometry; and the strip
+// geometry of the kernel made of `calls`: the library's own, or the requested
+// point with default_mat_params filling in what it leaves open.
+bool library_geometry(const MatParams& p);
+MatParams kernel_mat_params(const Script& s, const std::vector<int>& calls, const MatParams& req);
 int dtype_size(int dtype);
 // Geometry of a row-resident kernel on a rows x cols matrix after defaults:
 // W waves (WP: W rounded up to a power of two) that share a row, KP float4 per
@@ -128,6 +133,7 @@ struct KernelCode {
     std::string params_json;
     std::vector<int> calls;
     bool mat = false;
+    bool stream = false;           // rows streamed by whole waves (no gemtv, library geometry)
     // Row-resident kernels: the generator's estimate of the VGPRs per lane a row
     // group keeps live, and whether it exceeds the register budget (such a
     // kernel likely spills to scratch memory)

@@ -316,6 +316,84 @@ MatParams default_mat_params(int64_t rows, int64_t cols, const MatParams& req, i
     return p;
 }
 
+// The library's own strip geometry for a kernel whose caller asks for none: k, W
+// and G, and a number of row blocks that gives every CU the stated waves. Each
+// line was timed over square and uneven shapes from 128 to 32768 against ten to
+// fourteen others (whole plans, three inputs in turn; us at the sizes named):
+//  - small matrices (6M elements, about what stays in L2) are bound by latency and
+//    by the finishing launch, which wants few row blocks: four rows per step and
+//    wave. BiCGK n = 1024 5.7 (sixteen waves, two float4: 7.2); 2048 8.9 (10.4).
+//  - kernels that store a matrix mix reads and writes, and DRAM serves that best
+//    from eight waves a CU: GEMVER's first kernel n = 16384 346 (sixteen waves of
+//    the next line 413, 2048 small workgroups 361). Rows that do not start on
+//    1 KiB boundaries take two float4 per lane, as strip edges then cost part of a
+//    line on each side: n = 9000 131 (one float4: 163).
+//  - other FP32 kernels: one workgroup of sixteen waves per CU, 2 KiB strips. BiCGK
+//    n = 16384 165 (2048 workgroups of four waves: 186), 5003 21.3 (26.5), 12001 94
+//    (124), 700 x 16000 12.5 (22.6).
+//  - BF16 and FP8 in 16-byte units: three workgroups of eight waves per CU hide the
+//    conversion. BiCGK FP8 n = 16384 52 (77), BF16 85 (101). One or two strips leave
+//    row blocks only; sixteen waves a workgroup then halve their number
+//    (FP8 20000 x 700 15.4, 21 with eight).
+static MatParams library_mat_params(int64_t rows, int64_t cols, int E, bool stores) {
+    MatParams p;
+    int per_cu;
+    const bool small = (double)rows * (double)cols <= 6e6;
+    if (small) { p.k = 1; p.waves = 8; p.group = 4; per_cu = 16; }
+    else if (stores) { const bool line = cols % 256 == 0; p.k = line ? 1 : 2; p.waves = 8; p.group = line ? 4 : 2; per_cu = 8; }
+    else if (E == 4) { p.k = 2; p.waves = 16; p.group = 1; per_cu = 16; }
+    else if (cols <= 2 * 64 * E) { p.k = 1; p.waves = 16; p.group = 1; per_cu = 16; }
+    else { p.k = 1; p.waves = 8; p.group = 1; per_cu = 24; }
+    const int64_t C = 64LL * E * p.k, S = (cols + C - 1) / C, unit = p.waves * p.group;
+    const int64_t nb = std::max<int64_t>(1, 256 * per_cu / (S * p.waves));
+    int64_t r = (rows + nb - 1) / nb;
+    r = std::max<int64_t>((r + unit - 1) / unit * unit, p.waves * std::max(4, p.group));
+    // the row vectors of a block are staged in LDS
+    p.rows = (int)std::min<int64_t>(r, 4096 / unit * unit);
+    return p;
+}
+
+bool library_geometry(const MatParams& p) { return p.sched == 0 && p.k <= 0 && p.waves <= 0 && p.group <= 0 && p.rows <= 0; }
+
+MatParams kernel_mat_params(const Script& s, const std::vector<int>& calls, const MatParams& req) {
+    const Space sp = call_space(s, calls[0]);
+    const int E = kernel_unit_elems(s, calls, req.unit);
+    if (!library_geometry(req)) return default_mat_params(sp.a, sp.b, req, E);
+    const std::set<int> mine(calls.begin(), calls.end());
+    std::set<int> mats, cols, rows;
+    int gemtv = 0;
+    bool stores = false, ger = false;
+    for (int c : calls) {
+        const Call& k = s.calls[c];
+        const int prod = s.values[k.in[0]].producer;
+        if (prod < 0 || !mine.count(prod)) {
+            mats.insert(k.in[0]);
+            if (s.values[k.in[0]].scale >= 0) rows.insert(s.values[k.in[0]].scale);
+        }
+        if (k.op == Op::Gemtv) { ++gemtv; rows.insert(k.in[1]); }
+        if (k.op == Op::Gemv) cols.insert(k.in[1]);
+        if (k.op != Op::Ger) continue;
+        ger = true;
+        rows.insert(k.in[1]);
+        cols.insert(k.in[2]);
+        const Value& o = s.values[k.out];
+        stores = stores || o.output;
+        for (int d : o.consumers) stores = stores || !mine.count(d);
+    }
+    MatParams p = library_mat_params(sp.a, sp.b, E, stores);
+    p.unit = req.unit;
+    // kernels of so many operands that a lane's rows, vectors and accumulators
+    // outgrow the registers (128 with sixteen waves in a workgroup, 256 with
+    // eight) or the staged vectors and wave sums the LDS keep the small workgroups
+    const int K = p.k * E / 4;
+    const int regs = 4 * K * (p.group * (int)mats.size() + (int)cols.size() + gemtv + (ger ? 1 : 0));
+    const int64_t lds = (int64_t)rows.size() * p.rows * 4 + (int64_t)gemtv * p.waves * 64 * K * 16;
+    if (regs > (p.waves > 8 ? 72 : 168) || lds > 72 * 1024) {
+        p = default_mat_params(sp.a, sp.b, req, E);
+    }
+    return p;
+}
+
 VecParams default_vec_params(int64_t n, const VecParams& req) {
     VecParams p = req;
     if (p.unroll <= 0) p.unroll = 4;
