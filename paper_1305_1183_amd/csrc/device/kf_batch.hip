@@ -24,10 +24,9 @@
 //
 // Tile shape by size bucket. Up to n = 512: TPR = 2^LTPR lanes share a row (K
 // float4 chunks each), 256 / TPR rows are in flight per workgroup step, G =
-// 2^LG steps are loaded before their row sums are reduced. Above, BiCGK uses
-// the wide tiles, in which the four waves split the columns of each row
-// (below); GEMVER keeps whole rows per wave group there, which measured faster
-// for its B stores.
+// 2^LG steps are loaded before their row sums are reduced. Above, BiCGK and
+// the first phase of GEMVER let the four waves split the columns of each row
+// (below).
 #include <hip/hip_runtime.h>
 
 #include "device/kf_blocks.h"
@@ -53,15 +52,6 @@ __device__ __forceinline__ kf_f4 kfb_fold4(kf_f4 a) {
     } else {
         return a;
     }
-}
-
-// Sum of the column partials of a split instance's row blocks 0 .. nblk - 1
-// (p points at block 0's chunk, blocks ld floats apart), compensated, in
-// block order.
-__device__ __forceinline__ kf_f4 kfb_block_partials(const float* p, long ld, int nblk) {
-    kf_cs4 t = kf_cs4_init(kf_zero4());
-    for (int b = 0; b < nblk; ++b) t = kf_cs4_add(t, kf_ld4(p + (long)b * ld));
-    return kf_cs4_value(t);
 }
 
 // Column sums of acc[k] over the 256 / TPR row-lanes of the workgroup, in a
@@ -90,35 +80,69 @@ __device__ __forceinline__ void kfb_colsum(kf_f4* acc, kf_f4* red, Emit emit) {
     }
 }
 
-// Device-scope release and acquire, separately: a release writes back this
-// XCD's L2 so that other XCDs can read what the workgroup stored; an acquire
-// invalidates the local caches so that this workgroup reads what other XCDs
-// released. A full fence does both, and its invalidation drops lines every
-// other workgroup on the XCD is still using, so each side is used only where
-// it is needed.
-__device__ __forceinline__ void kfb_release() { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent"); }
-__device__ __forceinline__ void kfb_acquire() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
+// Data that another workgroup of the launch reads (column partials, x, and B of a
+// split instance) is stored through the XCD's L2 and loaded past it, access by
+// access, so publishing it takes a wait for the stores and no fence. A device-scope
+// release walks the whole L2 and an acquire empties it for every workgroup of the
+// XCD: 512 BiCGK + 512 GEMVER, n = 32 .. 2048, 965 us with fences and 815 without
+// (1024 BiCGK alone 454 and 344 us, 5.7 TB/s).
+typedef int kfb_i4 __attribute__((ext_vector_type(4)));
+constexpr int KFB_STREAM = 2;        // nt
+constexpr int KFB_DEV = 16;          // sc1: device scope
+constexpr int KFB_DEV_STREAM = 18;   // sc1 nt
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t kfb_rsrc(const float* p, long floats) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)(floats * 4), 0x00027000);
+}
+template <int AUX>
+__device__ __forceinline__ kf_f4 kfb_ld4_dev(__amdgpu_buffer_rsrc_t b, int off) {
+    return __builtin_bit_cast(kf_f4, __builtin_amdgcn_raw_buffer_load_b128(b, off * 4, 0, AUX));
+}
+template <int AUX>
+__device__ __forceinline__ void kfb_st4_dev(__amdgpu_buffer_rsrc_t b, int off, kf_f4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(kfb_i4, v), b, off * 4, 0, AUX);
+}
+// at lane offset `off` of the row that starts at the uniform offset `row`
+template <int AUX>
+__device__ __forceinline__ kf_f4 kfb_ld4_row(__amdgpu_buffer_rsrc_t b, int off, int row) {
+    return __builtin_bit_cast(kf_f4, __builtin_amdgcn_raw_buffer_load_b128(b, off * 4, row * 4, AUX));
+}
+// the first nv (0 .. 4) floats of v
+template <int AUX>
+__device__ __forceinline__ void kfb_st4_row(__amdgpu_buffer_rsrc_t b, int off, int row, int nv, kf_f4 v) {
+    if (nv >= 4) { __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(kfb_i4, v), b, off * 4, row * 4, AUX); return; }
+    if (nv > 0) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v.x), b, off * 4, row * 4, AUX);
+    if (nv > 1) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v.y), b, off * 4 + 4, row * 4, AUX);
+    if (nv > 2) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v.z), b, off * 4 + 8, row * 4, AUX);
+}
+template <int AUX>
+__device__ __forceinline__ void kfb_st4_dev_tail(__amdgpu_buffer_rsrc_t b, int off, int nv, kf_f4 v) {
+    if (nv >= 4) { kfb_st4_dev<AUX>(b, off, v); return; }
+    if (nv > 0) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v.x), b, off * 4, 0, KFB_DEV);
+    if (nv > 1) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v.y), b, off * 4 + 4, 0, KFB_DEV);
+    if (nv > 2) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v.z), b, off * 4 + 8, 0, KFB_DEV);
+}
+// Every store of the workgroup has reached the point that all XCDs share.
+__device__ __forceinline__ void kfb_stored() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
 
 // Arrival at a per-instance counter. Returns true in every thread of the
-// workgroup that arrives last; that workgroup then sees the stores every
-// earlier arrival made before arriving, and the counter is back at zero.
+// workgroup that arrives last, and the counter is back at zero. Device-scope
+// stores made before an arrival are visible to device-scope loads of the last.
 __device__ __forceinline__ bool kfb_arrive(unsigned* counter, unsigned count, int* s_flag) {
-    __syncthreads();
+    kfb_stored();
     if (threadIdx.x == 0) {
-        kfb_release();
-        const unsigned old = atomicAdd(counter, 1u);
+        const unsigned old = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const int last = old == count - 1;
-        if (last) {
-            kfb_acquire();
-            __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *s_flag = last;
     }
     __syncthreads();
     return *s_flag != 0;
 }
 
-// Arrival that publishes nothing (only counts): no fences. The K2 blocks of a
+// Arrival that publishes nothing (only counts): no wait for stores. The K2 blocks of a
 // split GEMVER instance use it to find the last one, which clears the
 // instance's flag for the next launch; every block has passed its wait on the
 // flag before it arrives, and the next launch starts after this one ends.
@@ -132,6 +156,15 @@ __device__ __forceinline__ bool kfb_count(unsigned* counter, unsigned count, int
     }
     __syncthreads();
     return *s_flag != 0;
+}
+
+// Sum of the column partials of a split instance's row blocks 0 .. nblk - 1
+// (ld floats apart) at columns col .. col + 3, compensated, in
+// block order.
+__device__ __forceinline__ kf_f4 kfb_block_partials(__amdgpu_buffer_rsrc_t p, int col, int ld, int nblk) {
+    kf_cs4 t = kf_cs4_init(kf_zero4());
+    for (int b = 0; b < nblk; ++b) t = kf_cs4_add(t, kfb_ld4_dev<KFB_DEV>(p, b * ld + col));
+    return kf_cs4_value(t);
 }
 
 // Chunk k of a thread covers columns col .. col + 3, col = 4 (cl + k TPR).
@@ -151,15 +184,22 @@ __device__ __forceinline__ kfb_cols kfb_col(int col, int n, int ld) {
 // clamped into the block (row r1 - 1, the row's last chunk) and entries of
 // rows >= r1 or columns >= n are replaced by zero with a select (padding may
 // hold NaN). Clamped loads fall on lines that other lanes fetch anyway.
-__device__ __forceinline__ kf_f4 kfb_ldm(const float* M, long ld, int row, int r1, kfb_cols c) {
-    const long rc = row < r1 ? row : r1 - 1;
-    kf_f4 v = kf_ld4_nt(M + rc * ld + c.cc);
+__device__ __forceinline__ kf_f4 kfb_mask(kf_f4 v, int row, int r1, kfb_cols c) {
     const int lim = row < r1 ? c.nv : 0;
     v.x = lim > 0 ? v.x : 0.f;
     v.y = lim > 1 ? v.y : 0.f;
     v.z = lim > 2 ? v.z : 0.f;
     v.w = lim > 3 ? v.w : 0.f;
     return v;
+}
+__device__ __forceinline__ kf_f4 kfb_ldm(const float* M, long ld, int row, int r1, kfb_cols c) {
+    const long rc = row < r1 ? row : r1 - 1;
+    return kfb_mask(kf_ld4_nt(M + rc * ld + c.cc), row, r1, c);
+}
+// the same of a matrix that other workgroups have stored
+__device__ __forceinline__ kf_f4 kfb_ldm(__amdgpu_buffer_rsrc_t M, int ld, int row, int r1, kfb_cols c) {
+    const int rc = row < r1 ? row : r1 - 1;
+    return kfb_mask(kfb_ld4_dev<KFB_DEV_STREAM>(M, rc * ld + c.cc), row, r1, c);
 }
 // Vector entries at one chunk (the vector holds exactly n floats; entries
 // at index >= n read as zero). 32-bit index arithmetic throughout.
@@ -221,7 +261,7 @@ __device__ __forceinline__ void kfb_stage(kf_f4* dst, const float* v, int n, int
     }
 }
 
-// Wait (thread 0, bounded) until the instance's x is published, then acquire.
+// Wait (thread 0, bounded) until the instance's x is published.
 // Returns false in every thread if the wait ran out (error bit set).
 __device__ __forceinline__ bool kfb_wait_x(unsigned* ctr, unsigned* sync, unsigned spin_limit, Shared& sh) {
     if (threadIdx.x == 0) {
@@ -235,7 +275,6 @@ __device__ __forceinline__ bool kfb_wait_x(unsigned* ctr, unsigned* sync, unsign
             }
             __builtin_amdgcn_s_sleep(8);
         }
-        kfb_acquire();
         sh.flag = ok;
     }
     __syncthreads();
@@ -245,14 +284,14 @@ __device__ __forceinline__ bool kfb_wait_x(unsigned* ctr, unsigned* sync, unsign
 }
 
 // w rows r0 .. r1 - 1 of alpha B x, x given per thread at its columns.
-template <int LTPR, int K, int LG>
-__device__ __forceinline__ void kfb_gemv_rows(const kfb_inst& I, const float* __restrict__ B,
+template <int LTPR, int K, int LG, typename Mat>
+__device__ __forceinline__ void kfb_gemv_rows(const kfb_inst& I, Mat B,
                                               float* __restrict__ w, int r0, int r1, const kf_f4* xv) {
     // xv: x in LDS, chunk c at xv[c]
     constexpr int TPR = 1 << LTPR, G = 1 << LG, RL = KFB_THREADS / TPR, RI = RL * G;
     const int tid = kfb_tid(), cl = tid & (TPR - 1), rl = tid >> LTPR;
     const int n = I.n;
-    const long ld = I.ld;
+    const int ld = I.ld;
     kfb_cols cs[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) cs[k] = kfb_col(4 * (cl + k * TPR), n, I.ld);
@@ -335,19 +374,21 @@ __device__ void kfb_bicgk(const kfb_inst& I, int blk, float* __restrict__ arena,
         kfb_colsum<LTPR, K>(acc, sh.red, [&](int c, kf_f4 v) { kfb_stv(s, 4 * c, n, v); });
         return;
     }
-    float* part = ws + I.ws + (long)blk * ld;
+    const __amdgpu_buffer_rsrc_t part = kfb_rsrc(ws + I.ws, (long)I.nblk * I.ld);
     kfb_colsum<LTPR, K>(acc, sh.red, [&](int c, kf_f4 v) {
-        if (4 * c < ld) kf_st4(part + 4 * c, v);
+        if (4 * c < I.ld) kfb_st4_dev<KFB_DEV>(part, blk * I.ld + 4 * c, v);
     });
     unsigned* ctr = sync + KFB_SYNC_HEADER + KFB_SYNC_PER_INST * I.sync;
     if (kfb_arrive(ctr, (unsigned)I.nblk, &sh.flag)) {
         for (int c = threadIdx.x; 4 * c < n; c += KFB_THREADS) {
-            kfb_stv(s, 4 * c, n, kfb_block_partials(ws + I.ws + 4 * c, ld, I.nblk));
+            kfb_stv(s, 4 * c, n, kfb_block_partials(part, 4 * c, I.ld, I.nblk));
         }
     }
 }
 
-template <int LTPR, int K, int LG>
+// SPLIT: one row block of several (B goes to other workgroups); otherwise the
+// whole instance.
+template <int LTPR, int K, int LG, bool SPLIT>
 __device__ void kfb_gemver_k1(const kfb_inst& I, int blk, float* __restrict__ arena, float* __restrict__ ws,
                               unsigned* sync, Shared& sh) {
     constexpr int TPR = 1 << LTPR, G = 1 << LG, RL = KFB_THREADS / TPR, RI = RL * G;
@@ -365,6 +406,8 @@ __device__ void kfb_gemver_k1(const kfb_inst& I, int blk, float* __restrict__ ar
     const float* __restrict__ z = arena + I.v[5];
     float* __restrict__ x = arena + I.v[6];
     float* __restrict__ w = arena + I.v[7];
+    const __amdgpu_buffer_rsrc_t Bs = kfb_rsrc(B, n * ld);
+    (void)Bs;
     kf_f4 acc[K];
     kfb_cols cs[K];
     kfb_stage<LTPR, K>(sh.cv[0], v1, n, tid);
@@ -396,17 +439,20 @@ __device__ void kfb_gemver_k1(const kfb_inst& I, int blk, float* __restrict__ ar
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int row = i0 + g * RL + rl;
-            float* brow = B + (long)row * ld;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 kf_f4 b = kf_fma4s(u1r[g], v1c[k * TPR], a[g][k]);
                 b = kf_fma4s(u2r[g], v2c[k * TPR], b);
-                if (row < r1) kfb_stm(brow, 4 * (cl + k * TPR), n, b);
+                if constexpr (SPLIT) {
+                    if (row < r1) kfb_st4_dev_tail<KFB_DEV_STREAM>(Bs, row * I.ld + 4 * (cl + k * TPR), cs[k].nv, b);
+                } else {
+                    if (row < r1) kfb_stm(B + (long)row * ld, 4 * (cl + k * TPR), n, b);
+                }
                 acc[k] = kf_fma4s(yr[g], b, acc[k]);
             }
         }
     }
-    if (I.nblk == 1) {
+    if constexpr (!SPLIT) {
         // x is complete inside this workgroup: finish it, then run the gemv.
         kfb_colsum<LTPR, K>(acc, sh.red, [&](int c, kf_f4 v) {
             const kf_f4 xc = kf_fma4s(I.beta, v, kfb_ldv(z, 4 * c, n));
@@ -414,45 +460,24 @@ __device__ void kfb_gemver_k1(const kfb_inst& I, int blk, float* __restrict__ ar
             sh.cv[0][c] = xc;
         });
         __syncthreads();
-        kfb_gemv_rows<LTPR, K, LG>(I, B, w, 0, n, sh.cv[0]);
+        kfb_gemv_rows<LTPR, K, LG>(I, (const float*)B, w, 0, n, sh.cv[0]);
         return;
     }
-    float* part = ws + I.ws + (long)blk * ld;
+    const __amdgpu_buffer_rsrc_t part = kfb_rsrc(ws + I.ws, (long)I.nblk * I.ld);
     kfb_colsum<LTPR, K>(acc, sh.red, [&](int c, kf_f4 v) {
-        if (4 * c < ld) kf_st4(part + 4 * c, v);
+        if (4 * c < I.ld) kfb_st4_dev<KFB_DEV>(part, blk * I.ld + 4 * c, v);
     });
+    const __amdgpu_buffer_rsrc_t xs = kfb_rsrc(x, n);
     unsigned* ctr = sync + KFB_SYNC_HEADER + KFB_SYNC_PER_INST * I.sync;
     if (kfb_arrive(ctr, (unsigned)I.nblk, &sh.flag)) {
         for (int c = threadIdx.x; 4 * c < n; c += KFB_THREADS) {
-            const kf_f4 t = kfb_block_partials(ws + I.ws + 4 * c, ld, I.nblk);
-            kfb_stv(x, 4 * c, n, kf_fma4s(I.beta, t, kfb_ldv(z, 4 * c, n)));
+            const kf_f4 t = kfb_block_partials(part, 4 * c, I.ld, I.nblk);
+            kfb_st4_dev_tail<KFB_DEV>(xs, 4 * c, n - 4 * c, kf_fma4s(I.beta, t, kfb_ldv(z, 4 * c, n)));
         }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            kfb_release();
-            __hip_atomic_store(ctr + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        kfb_stored();
+        if (threadIdx.x == 0) __hip_atomic_store(ctr + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
-
-template <int LTPR, int K, int LG>
-__device__ void kfb_gemver_k2(const kfb_inst& I, int blk, float* __restrict__ arena, unsigned* sync,
-                              unsigned spin_limit, Shared& sh) {
-    const int n = I.n;
-    unsigned* ctr = sync + KFB_SYNC_HEADER + KFB_SYNC_PER_INST * I.sync;
-    if (!kfb_wait_x(ctr, sync, spin_limit, sh)) return;
-    const float* __restrict__ B = arena + I.b;
-    const float* __restrict__ x = arena + I.v[6];
-    float* __restrict__ w = arena + I.v[7];
-    kfb_stage<LTPR, K>(sh.cv[0], x, n, kfb_tid());
-    __syncthreads();
-    const int r0 = blk * I.rows, r1 = min(n, r0 + I.rows);
-    kfb_gemv_rows<LTPR, K, LG>(I, B, w, r0, r1, sh.cv[0]);
-    // the last K2 block of the instance clears the flag for the next launch
-    if (kfb_count(ctr + 2, (unsigned)I.nblk, &sh.flag) && threadIdx.x == 0)
-        __hip_atomic_store(ctr + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 
 // ---- wide BiCGK tiles (n > 512): the four waves split each row's columns ---
 // Lane t of the workgroup owns chunks t + 256 k (k < K) of every row of the
@@ -548,16 +573,195 @@ __device__ void kfb_w_bicgk(const kfb_inst& I, int blk, float* __restrict__ aren
         for (int k = 0; k < K; ++k) kfb_stv(s, 4 * (t + 256 * k), n, acc[k]);
         return;
     }
-    float* part = ws + I.ws + (long)blk * ld;
+    const __amdgpu_buffer_rsrc_t part = kfb_rsrc(ws + I.ws, (long)I.nblk * I.ld);
 #pragma unroll
     for (int k = 0; k < K; ++k)
-        if (4 * (t + 256 * k) < I.ld) kf_st4(part + 4 * (t + 256 * k), acc[k]);
+        if (4 * (t + 256 * k) < I.ld) kfb_st4_dev<KFB_DEV>(part, blk * I.ld + 4 * (t + 256 * k), acc[k]);
     unsigned* ctr = sync + KFB_SYNC_HEADER + KFB_SYNC_PER_INST * I.sync;
     if (kfb_arrive(ctr, (unsigned)I.nblk, &sh.flag)) {
         for (int c = threadIdx.x; 4 * c < n; c += KFB_THREADS) {
-            kfb_stv(s, 4 * c, n, kfb_block_partials(ws + I.ws + 4 * c, ld, I.nblk));
+            kfb_stv(s, 4 * c, n, kfb_block_partials(part, 4 * c, I.ld, I.nblk));
         }
     }
+}
+
+// ---- GEMVER with whole waves per row (n > 128) --------------------------------
+// Rows are wave-uniform, so an address is a scalar row offset plus one lane
+// register per chunk, and the next step's loads are issued before this step's
+// stores of B: loads and stores retire in one order, and a wait for loads behind
+// device-scope stores would be a wait for those too. Bound by HBM (A read, B
+// written, B read again): 512 BiCGK + 512 GEMVER 815 -> 780 us, 300 + 300 of n =
+// 600 .. 1000 673 -> 584; few instances by the latency of a step: 8 GEMVER of n =
+// 1000 131 -> 74 us.
+
+// w rows r0 .. r1 - 1 of alpha B x, a wave per row, x in LDS (zero past n).
+template <int K, int LG, int AUX>
+__device__ __forceinline__ void kfb_w_gemv(const kfb_inst& I, __amdgpu_buffer_rsrc_t B, float* __restrict__ w, int r0,
+                                           int r1, const kf_f4* xv) {
+    constexpr int G = 1 << LG;
+    const int t = kfb_tid(), lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int n = I.n, ld = I.ld;
+    kfb_cols cs[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) cs[k] = kfb_col(4 * (lane + 64 * k), n, ld);
+    kf_f4 bn[G][K];
+    auto load = [&](int base) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int rc = base + g < r1 ? base + g : r1 - 1;
+#pragma unroll
+            for (int k = 0; k < K; ++k) bn[g][k] = kfb_ld4_row<AUX>(B, cs[k].cc, rc * ld);
+        }
+    };
+    int i = r0 + wave * G;
+    load(i);
+#pragma unroll 1
+    for (; i < r1; i += 4 * G) {
+        kfb_reload_lds();
+        kf_f4 b[G][K];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int k = 0; k < K; ++k) b[g][k] = kfb_mask(bn[g][k], 0, 1, cs[k]);
+        if (i + 4 * G < r1) load(i + 4 * G);
+        float wp[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            wp[g] = 0.f;
+#pragma unroll
+            for (int k = 0; k < K; ++k) wp[g] = kf_dot4(b[g][k], xv[lane + 64 * k], wp[g]);
+        }
+        const float s = kfb_rows_reduce<6, LG>(wp);
+        const int row = i + (lane >> (6 - LG));
+        if ((lane & ((64 >> LG) - 1)) == 0 && row < r1) w[row] = I.alpha * s;
+    }
+}
+
+// K1: WC waves share a row (4 above n = 512: lane t of the workgroup owns chunks
+// t + 256 k of every row and its column sums need no exchange; 1 below: four row
+// groups whose column sums meet in LDS). A step's G rows are summed first, which
+// keeps the FP32 chains short.
+template <int WC, int K, int LG, bool SPLIT>
+__device__ void kfb_w_gemver_k1(const kfb_inst& I, int blk, float* __restrict__ arena, float* __restrict__ ws,
+                                unsigned* sync, Shared& sh) {
+    constexpr int G = 1 << LG, CT = 64 * WC, RW = 4 / WC * G, AUX = SPLIT ? KFB_DEV_STREAM : KFB_STREAM;
+    const int t = kfb_tid(), wave = __builtin_amdgcn_readfirstlane(t >> 6), ct = t & (CT - 1);
+    const int n = I.n, ld = I.ld;
+    const int r0 = blk * I.rows, r1 = min(n, r0 + I.rows);
+    const __amdgpu_buffer_rsrc_t A = kfb_rsrc(arena + I.a, n * ld), B = kfb_rsrc(arena + I.b, n * ld);
+    const float* __restrict__ u1 = arena + I.v[0];
+    const float* __restrict__ u2 = arena + I.v[2];
+    const float* __restrict__ y = arena + I.v[4];
+    const float* __restrict__ z = arena + I.v[5];
+    float* __restrict__ x = arena + I.v[6];
+    kf_f4 v1[K], v2[K], acc[K];
+    kfb_cols cs[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int col = 4 * (ct + CT * k);
+        cs[k] = kfb_col(col, n, ld);
+        v1[k] = kfb_ldv(arena + I.v[1], col, n);
+        v2[k] = kfb_ldv(arena + I.v[3], col, n);
+        acc[k] = kf_zero4();
+    }
+    kf_f4 an[G][K];
+    float u1n, u2n, yn;
+    auto load = [&](int base) {
+        u1n = kfb_row_fetch<G>(u1, base, r1);
+        u2n = kfb_row_fetch<G>(u2, base, r1);
+        yn = kfb_row_fetch<G>(y, base, r1);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int rc = base + g < r1 ? base + g : r1 - 1;
+#pragma unroll
+            for (int k = 0; k < K; ++k) an[g][k] = kfb_ld4_row<KFB_STREAM>(A, cs[k].cc, rc * ld);
+        }
+    };
+    int i = r0 + (WC == 4 ? 0 : wave * G);
+    load(i);
+#pragma unroll 1
+    for (; i < r1; i += RW) {
+        float u1r[G], u2r[G], yr[G];
+        kfb_row_bcast<G>(u1n, u1r);
+        kfb_row_bcast<G>(u2n, u2r);
+        kfb_row_bcast<G>(yn, yr);
+        kf_f4 b[G][K], s[K];
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int k = 0; k < K; ++k) b[g][k] = kf_fma4s(u2r[g], v2[k], kf_fma4s(u1r[g], v1[k], an[g][k]));
+        if (i + RW < r1) load(i + RW);
+#pragma unroll
+        for (int k = 0; k < K; ++k) s[k] = kf_mul4s(yr[0], b[0][k]);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (i + g < r1) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    if (g > 0) s[k] = kf_fma4s(yr[g], b[g][k], s[k]);
+                    kfb_st4_row<AUX>(B, 4 * (ct + CT * k), (i + g) * ld, cs[k].nv, b[g][k]);
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) acc[k] += s[k];
+    }
+    // column sums of the block at chunk c, each chunk from one thread
+    auto columns = [&](auto emit) {
+        if constexpr (WC == 4) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) emit(t + 256 * k, acc[k]);
+        } else {
+            kfb_colsum<6, K>(acc, sh.red, emit);
+        }
+    };
+    const __amdgpu_buffer_rsrc_t xs = kfb_rsrc(x, n);
+    if constexpr (!SPLIT) {
+        // x is complete inside this workgroup: finish it, then run the gemv.
+        columns([&](int c, kf_f4 v) {
+            const kf_f4 xc = 4 * c < n ? kf_fma4s(I.beta, v, kfb_ldv(z, 4 * c, n)) : kf_zero4();
+            kfb_stv(x, 4 * c, n, xc);
+            sh.cv[0][c] = kfb_mask(xc, 0, 1, kfb_col(4 * c, n, ld));
+        });
+        __syncthreads();
+        kfb_w_gemv<K * WC, (WC == 4 ? LG - 2 : LG), KFB_STREAM>(I, B, arena + I.v[7], 0, n, sh.cv[0]);
+        return;
+    }
+    const __amdgpu_buffer_rsrc_t part = kfb_rsrc(ws + I.ws, (long)I.nblk * ld);
+    columns([&](int c, kf_f4 v) {
+        if (4 * c < ld) kfb_st4_dev<KFB_DEV>(part, blk * ld + 4 * c, v);
+    });
+    unsigned* ctr = sync + KFB_SYNC_HEADER + KFB_SYNC_PER_INST * I.sync;
+    if (kfb_arrive(ctr, (unsigned)I.nblk, &sh.flag)) {
+        for (int c = threadIdx.x; 4 * c < n; c += KFB_THREADS) {
+            const kf_f4 v = kfb_block_partials(part, 4 * c, ld, I.nblk);
+            kfb_st4_dev_tail<KFB_DEV>(xs, 4 * c, n - 4 * c, kf_fma4s(I.beta, v, kfb_ldv(z, 4 * c, n)));
+        }
+        kfb_stored();
+        if (threadIdx.x == 0) __hip_atomic_store(ctr + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// K2 block of a split instance: CHUNKS float4 cover x; gemv(B, r0, r1) walks the
+// block's rows.
+template <int CHUNKS, typename Gemv>
+__device__ __forceinline__ void kfb_gemver_k2(const kfb_inst& I, int blk, float* __restrict__ arena, unsigned* sync,
+                                              unsigned spin_limit, Shared& sh, Gemv gemv) {
+    const int n = I.n;
+    unsigned* ctr = sync + KFB_SYNC_HEADER + KFB_SYNC_PER_INST * I.sync;
+    if (!kfb_wait_x(ctr, sync, spin_limit, sh)) return;
+    // (a vector's place in the arena is a multiple of 64 floats)
+    const __amdgpu_buffer_rsrc_t x = kfb_rsrc(arena + I.v[6], (n + 3) / 4 * 4);
+    for (int c = threadIdx.x; c < CHUNKS; c += KFB_THREADS) {
+        const kfb_cols cx = kfb_col(4 * c, n, (n + 3) / 4 * 4);
+        sh.cv[0][c] = kfb_mask(kfb_ld4_dev<KFB_DEV>(x, cx.cc), 0, 1, cx);
+    }
+    __syncthreads();
+    const int r0 = blk * I.rows, r1 = min(n, r0 + I.rows);
+    gemv(kfb_rsrc(arena + I.b, n * I.ld), r0, r1);
+    // the last K2 block of the instance clears the flag for the next launch
+    if (kfb_count(ctr + 2, (unsigned)I.nblk, &sh.flag) && threadIdx.x == 0)
+        __hip_atomic_store(ctr + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Tile T of the menu of (KIND, B), instantiated from the shared table.
@@ -567,14 +771,29 @@ __device__ __forceinline__ void kfb_tile_run(const kfb_inst& I, int phase, int b
     constexpr kfb_tile x = kfb_tile_menu[KIND][B][T];
     if constexpr (x.k == 0) {
         return;   // not on the menu (the host never selects it)
-    } else if constexpr (x.wide) {
+    } else if constexpr (KIND == 0 && x.wide) {
         kfb_w_bicgk<x.k, x.lg>(I, blk, arena, ws, sync, sh);
     } else if constexpr (KIND == 0) {
         kfb_bicgk<x.ltpr, x.k, x.lg>(I, blk, arena, ws, sync, sh);
+    } else if constexpr (x.ltpr == 6) {
+        // whole waves per row; from four chunks a lane on, K1's waves share the rows
+        // of a step instead of taking them in turn (the same rows per step)
+        constexpr int WC = x.k >= 4 ? 4 : 1, K = x.k / WC, LG = WC == 4 ? x.lg + 2 : x.lg;
+        if (phase == KFB_GEMVER_K1) {
+            if (I.nblk == 1) kfb_w_gemver_k1<WC, K, LG, false>(I, blk, arena, ws, sync, sh);
+            else kfb_w_gemver_k1<WC, K, LG, true>(I, blk, arena, ws, sync, sh);
+        } else {
+            kfb_gemver_k2<64 * x.k>(I, blk, arena, sync, spin_limit, sh, [&](__amdgpu_buffer_rsrc_t Bm, int r0, int r1) {
+                kfb_w_gemv<x.k, x.lg, KFB_DEV_STREAM>(I, Bm, arena + I.v[7], r0, r1, sh.cv[0]);
+            });
+        }
     } else if (phase == KFB_GEMVER_K1) {
-        kfb_gemver_k1<x.ltpr, x.k, x.lg>(I, blk, arena, ws, sync, sh);
+        if (I.nblk == 1) kfb_gemver_k1<x.ltpr, x.k, x.lg, false>(I, blk, arena, ws, sync, sh);
+        else kfb_gemver_k1<x.ltpr, x.k, x.lg, true>(I, blk, arena, ws, sync, sh);
     } else {
-        kfb_gemver_k2<x.ltpr, x.k, x.lg>(I, blk, arena, sync, spin_limit, sh);
+        kfb_gemver_k2<(x.k << x.ltpr)>(I, blk, arena, sync, spin_limit, sh, [&](__amdgpu_buffer_rsrc_t Bm, int r0, int r1) {
+            kfb_gemv_rows<x.ltpr, x.k, x.lg>(I, Bm, arena + I.v[7], r0, r1, sh.cv[0]);
+        });
     }
 }
 
@@ -601,8 +820,8 @@ __device__ __forceinline__ void kfb_kind_run(const kfb_inst& I, int phase, int b
     }
 }
 
-// Three waves per SIMD (168 VGPRs, two of them spilled): the whole-row GEMVER
-// tiles of the largest bucket keep eight 16-byte loads per lane in flight.
+// Three waves per SIMD (168 VGPRs): GEMVER's steps of eight 16-byte loads per lane
+// keep the next step's loads beside them.
 __global__ void __launch_bounds__(KFB_THREADS) __attribute__((amdgpu_waves_per_eu(3, 8)))
 kfb_kernel(const kfb_inst* __restrict__ insts, const kfb_item* __restrict__ items, int nitems, int item0,
            int persistent, float* arena, float* ws, unsigned* sync, unsigned spin_limit) {
@@ -622,9 +841,7 @@ kfb_kernel(const kfb_inst* __restrict__ insts, const kfb_item* __restrict__ item
         const kfb_inst I = insts[item.inst];
         const int phase = item.phase_blk >> 24;
         const int blk = item.phase_blk & 0xffffff;
-        // the instance's tile from the menu of its kind and size bucket (by
-        // default BiCGK takes the wide tiles above n = 512; GEMVER keeps whole
-        // rows per wave there, which stores B faster, measured per bucket)
+        // the instance's tile from the menu of its kind and size bucket
         if (I.kind == 0) kfb_kind_run<0>(I, phase, blk, arena, ws, sync, spin_limit, sh);   // BiCGK
         else kfb_kind_run<1>(I, phase, blk, arena, ws, sync, spin_limit, sh);
         if (!persistent) break;

@@ -59,7 +59,9 @@ static inline int kfb_bucket(int n) {
 // (TPR K 4 >= the bucket's largest n), and walks 256 / TPR rows per step, G =
 // 2^LG steps per row reduction. A wide tile (BiCGK above n = 512) lets the
 // four waves split each row, K float4 chunks per lane of the workgroup, G =
-// 2^LG rows per step. Entries with k = 0 are absent.
+// 2^LG rows per step. GEMVER's tiles of TPR = 64 and K >= 4 take the same rows per
+// step in their first phase with the four waves splitting each row. Entries with
+// k = 0 are absent.
 #define KFB_TILES 3
 struct kfb_tile {
     int8_t wide, ltpr, k, lg;
