@@ -158,12 +158,26 @@ __device__ __forceinline__ bool kfb_count(unsigned* counter, unsigned count, int
     return *s_flag != 0;
 }
 
+// Sixteen loads are in flight: one at a time, each waits for memory past the L2, and
+// x of a GEMVER instance for all of them (n = 2048 in 32 blocks: 90 -> 78 us).
+constexpr int KFB_AHEAD = 16;
 // Sum of the column partials of a split instance's row blocks 0 .. nblk - 1
 // (ld floats apart) at columns col .. col + 3, compensated, in
 // block order.
 __device__ __forceinline__ kf_f4 kfb_block_partials(__amdgpu_buffer_rsrc_t p, int col, int ld, int nblk) {
     kf_cs4 t = kf_cs4_init(kf_zero4());
-    for (int b = 0; b < nblk; ++b) t = kf_cs4_add(t, kfb_ld4_dev<KFB_DEV>(p, b * ld + col));
+#pragma unroll 1
+    for (int b0 = 0; b0 < nblk; b0 += KFB_AHEAD) {
+        kf_f4 v[KFB_AHEAD];
+#pragma unroll
+        for (int j = 0; j < KFB_AHEAD; ++j) {
+            const int b = b0 + j < nblk ? b0 + j : nblk - 1;
+            v[j] = kfb_ld4_row<KFB_DEV>(p, col, b * ld);
+        }
+#pragma unroll
+        for (int j = 0; j < KFB_AHEAD; ++j)
+            if (b0 + j < nblk) t = kf_cs4_add(t, v[j]);
+    }
     return kf_cs4_value(t);
 }
 
