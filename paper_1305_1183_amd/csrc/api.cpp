@@ -857,7 +857,7 @@ static kf_status launch_kernel(kf_plan* p, PlanKernel& k, hipStream_t stream, vo
             const int64_t NP = (p->rt_n + 3) / 4 * 4;
             grid = l.dyn_grid == 1 ? S * NB
                                    : (l.dyn_rpart ? (p->rt_m + l.dyn_fwb - 1) / l.dyn_fwb : 0) +
-                                         (l.dyn_cpart ? (NP / 4 + 63) / 64 : 0);
+                                         (l.dyn_cpart ? (NP / 4 + kf::kFinishCols - 1) / kf::kFinishCols : 0);
         }
         for (size_t i = 0; i < na; ++i) {
             const KArg& a = l.args[i];

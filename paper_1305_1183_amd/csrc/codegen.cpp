@@ -126,15 +126,21 @@ void kernel_bytes(const Script& s, const std::vector<int>& calls, const std::vec
     *wr = w;
 }
 
-// Finishing launch of column partials (both BLAS-2 schedules): for columns
-// cc .. cc + 3, wave `wave` of FW adds row blocks wave, wave + FW, ... of each
-// gemtv call's partials, compensated; the FW wave pairs are merged in wave
-// order through LDS (one buffer, reused call by call) and wave 0 ends with
-// sum<c> (zero in the other waves). Expects lane, wave, cc, N, NB, NP, FW
-// and ws in scope; every barrier is outside divergent code.
+// Finishing launch of column partials (both BLAS-2 schedules): a workgroup takes
+// FC float4 columns, and the 64 / FC lane groups of its FW waves split the row
+// blocks. Group gid adds blocks gid, gid + FWG, ... of each gemtv call's partials at
+// columns cc .. cc + 3, compensated; the groups of a wave and then the waves (in
+// wave order, through LDS, one buffer reused call by call) are merged as pairs,
+// and lanes below FC of wave 0 end with sum<c>. Expects lane, wave, cc, N, NB, NP,
+// FW, FC and ws in scope; every barrier is outside divergent code.
+// Bound by latency, not bytes (1 MB for 256 blocks of 1021 columns): 16 columns a
+// workgroup give four times the workgroups of 64 and a quarter of the loads
+// per lane (that launch 6.3 -> 4.6 us; 64 blocks of 1024 columns 3.4 -> 3.0).
 static void emit_colpart_finish(Emitter& f, const std::vector<int>& gemtv_calls,
                                 const std::map<int, size_t>& ws_off) {
-    f.l("__shared__ kf_f4 kf_fr[2][FW][64];");
+    f.l("__shared__ kf_f4 kf_fr[2][FW][FC];");
+    f.l("constexpr int FWG = FW * (64 / FC);");
+    f.l("const int gid = wave * (64 / FC) + lane / FC;");
     bool first = true;
     for (int c : gemtv_calls) {
         const size_t off = ws_off.at(c);
@@ -142,18 +148,19 @@ static void emit_colpart_finish(Emitter& f, const std::vector<int>& gemtv_calls,
         // flight together rather than one latency per row block
         f.l(F("kf_cs4 pc%d = kf_cs4_init(kf_zero4());", c));
         f.l("if (cc < N) {");
-        f.l("  for (long b0 = wave; b0 < NB; b0 += 8 * FW) {");
+        f.l("  for (long b0 = gid; b0 < NB; b0 += 8 * FWG) {");
         f.l("    kf_f4 pv[8];");
-        f.l(F("    for (int i = 0; i < 8; ++i) { const long b = b0 + (long)i * FW; pv[i] = b < NB ? kf_ld4(ws + %zuL + b * NP + cc) : kf_zero4(); }", off));
-        f.l(F("    for (int i = 0; i < 8; ++i) if (b0 + (long)i * FW < NB) pc%d = kf_cs4_add(pc%d, pv[i]);", c, c));
+        f.l(F("    for (int i = 0; i < 8; ++i) { const long b = b0 + (long)i * FWG; pv[i] = b < NB ? kf_ld4(ws + %zuL + b * NP + cc) : kf_zero4(); }", off));
+        f.l(F("    for (int i = 0; i < 8; ++i) if (b0 + (long)i * FWG < NB) pc%d = kf_cs4_add(pc%d, pv[i]);", c, c));
         f.l("  }");
         f.l("}");
+        f.l(F("for (int m = 32; m >= FC; m >>= 1) pc%d = kf_cs4_merge(pc%d, kf_cs4_down(pc%d, m));", c, c, c));
         if (!first) f.l("__syncthreads();");
         first = false;
-        f.l(F("kf_fr[0][wave][lane] = pc%d.s; kf_fr[1][wave][lane] = pc%d.c;", c, c));
+        f.l(F("if (lane < FC) { kf_fr[0][wave][lane] = pc%d.s; kf_fr[1][wave][lane] = pc%d.c; }", c, c));
         f.l("__syncthreads();");
         f.l(F("kf_f4 sum%d = kf_zero4();", c));
-        f.l("if (wave == 0) {");
+        f.l("if (wave == 0 && lane < FC) {");
         f.l("  kf_cs4 t = {kf_fr[0][0][lane], kf_fr[1][0][lane]};");
         f.l("  for (int w = 1; w < FW; ++w) { const kf_cs4 o = {kf_fr[0][w][lane], kf_fr[1][w][lane]}; t = kf_cs4_merge(t, o); }");
         f.l(F("  sum%d = kf_cs4_value(t);", c));
@@ -284,7 +291,8 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     e.l("const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;");
     e.l("const long sidx = blockIdx.x % S, rb = blockIdx.x / S;");
     // NB row blocks of equal size, at most R rows each
-    e.l("const long c0 = sidx * C, r0 = rb * M / NB, r1 = (rb + 1) * M / NB;");
+    if (!p.dyn && M % NB == 0) e.l("const long c0 = sidx * C, r0 = rb * (M / NB), r1 = r0 + M / NB;");
+    else e.l("const long c0 = sidx * C, r0 = rb * M / NB, r1 = (rb + 1) * M / NB;");
     e.l("(void)ws;");
     for (int v : scalars) {
         if (s.values[v].kind == VK::Const) e.l(F("const float %s = P%d;", scal_name(v).c_str(), v));
@@ -566,7 +574,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         fsig.push_back("const float* __restrict__ ws");
         const int FWb = (col_part && NB >= 64) ? 1024 : 256;
         const long RBK = row_part ? (M + FWb - 1) / FWb : 0;
-        const long CBK = col_part ? (NP / 4 + 63) / 64 : 0;
+        const long CBK = col_part ? (NP / 4 + kFinishCols - 1) / kFinishCols : 0;
         const int FW = NB >= 64 ? 16 : 4;   // waves of the finishing pass that split the row blocks
         if (p.dyn) {
             finl.args.push_back({ArgKind::ShapeM, -1});
@@ -580,7 +588,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         } else {
             f.l(F("constexpr long M = %ldL, N = %ldL, S = %ldL, NB = %ldL, NP = %ldL, RBK = %ldL;", M, N, S, NB, NP, RBK));
         }
-        f.l(F("constexpr int FW = %d; (void)FW;", FW));
+        f.l(F("constexpr int FW = %d, FC = %d; (void)FW; (void)FC;", FW, kFinishCols));
         for (int v : scalars) {
             if (s.values[v].kind == VK::Const) f.l(F("const float %s = P%d;", scal_name(v).c_str(), v));
             else f.l(F("const float %s = *P%d;", scal_name(v).c_str(), v));
@@ -615,15 +623,12 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
             f.l("}");
         }
         if (col_part) {
-            // 64 float4 columns per workgroup; the FW waves split the row blocks
-            // (wave w adds blocks w, w + FW, ...) and are merged in wave order,
-            // all of it compensated.
             f.l("if (blockIdx.x >= RBK) {");
             f.ind++;
             f.l("const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;");
-            f.l("const long cc = 4L * ((long)(blockIdx.x - RBK) * 64 + lane);");
+            f.l("const long cc = 4L * ((long)(blockIdx.x - RBK) * FC + lane % FC);");
             emit_colpart_finish(f, gemtv_calls, ws_off);
-            f.l("if (wave == 0 && cc < N) {");
+            f.l("if (wave == 0 && lane < FC && cc < N) {");
             f.ind++;
             for (int c : gemtv_calls) {
                 const Call& k = s.calls[c];
@@ -1670,11 +1675,11 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
             f.l(s.values[v].kind == VK::Const ? F("const float %s = P%d;", scal_name(v).c_str(), v)
                                               : F("const float %s = *P%d;", scal_name(v).c_str(), v));
         const int FW = NB >= 64 ? 16 : 4;   // waves that split the row blocks
-        f.l(F("constexpr int FW = %d;", FW));
+        f.l(F("constexpr int FW = %d, FC = %d;", FW, kFinishCols));
         f.l("const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;");
-        f.l("const long cc = 4L * ((long)blockIdx.x * 64 + lane);");
+        f.l("const long cc = 4L * ((long)blockIdx.x * FC + lane % FC);");
         emit_colpart_finish(f, gemtv_calls, ws_off);
-        f.l("if (wave == 0 && cc < N) {");
+        f.l("if (wave == 0 && lane < FC && cc < N) {");
         f.ind++;
         for (size_t i = 0; i < gemtv_calls.size(); ++i) {
             int c = gemtv_calls[i];
@@ -1691,7 +1696,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         }
         f.ind--;
         f.l("}");
-        finl.grid = (int)((NP / 4 + 63) / 64);
+        finl.grid = (int)((NP / 4 + kFinishCols - 1) / kFinishCols);
         finl.block = 64 * FW;
     }
     std::string sigs, fsigs;

@@ -330,6 +330,18 @@ __device__ __forceinline__ kf_f4 kf_cs4_value(kf_cs4 a) {
     return r;
 }
 
+// The pairs of lane l + m (the low lanes of the wave; the others get some lane's).
+__device__ __forceinline__ kf_cs4 kf_cs4_down(kf_cs4 a, int m) {
+    const int at = 4 * (int)(__lane_id() + m);
+    kf_cs4 r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        r.s[i] = __int_as_float(__builtin_amdgcn_ds_bpermute(at, __float_as_int(a.s[i])));
+        r.c[i] = __int_as_float(__builtin_amdgcn_ds_bpermute(at, __float_as_int(a.c[i])));
+    }
+    return r;
+}
+
 // Butterfly within aligned groups of NL lanes (NL a power of two, at most 64)
 // on pairs: every lane of a group ends with the merge of the group's pairs.
 template <int NL>

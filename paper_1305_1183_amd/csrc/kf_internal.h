@@ -108,6 +108,9 @@ enum class ArgKind : int {
 };
 struct KArg { ArgKind kind; int value; };   // value id (or -1 for the workspace)
 
+// float4 columns per workgroup of a finishing launch
+constexpr int kFinishCols = 16;
+
 // One HIP kernel launch: the main pass of a plan kernel, or the pass that
 // finishes its cross-workgroup reductions.
 struct Launch {
@@ -117,7 +120,7 @@ struct Launch {
     uint64_t bytes_read = 0, bytes_written = 0;   // algorithmic HBM bytes of this launch
     // Runtime-shape plans compute the grid from the shape of each run:
     // dyn_grid 1 = strips x row blocks (S NB), 2 = finishing launch (row blocks
-    // of rows plus column groups of 64 float4).
+    // of rows plus column groups of kFinishCols float4).
     int dyn_grid = 0;
     long dyn_c = 0, dyn_r = 0, dyn_fwb = 0;
     bool dyn_rpart = false, dyn_cpart = false;
