@@ -126,6 +126,12 @@ void kernel_bytes(const Script& s, const std::vector<int>& calls, const std::vec
     *wr = w;
 }
 
+// Waves that split the row blocks: four lane groups each, so that a group's share
+// is about one round of eight loads (80 blocks of 9811 columns with sixteen waves 4.9 us,
+// more merging than adding, with four 3.8; 256 of 1021 columns with sixteen 4.6, with
+// eight 3.9).
+static int finish_waves(long NB) { return NB > 128 ? 8 : 4; }
+
 // Finishing launch of column partials (both BLAS-2 schedules): a workgroup takes
 // FC float4 columns, and the 64 / FC lane groups of its FW waves split the row
 // blocks. Group gid adds blocks gid, gid + FWG, ... of each gemtv call's partials at
@@ -135,7 +141,7 @@ void kernel_bytes(const Script& s, const std::vector<int>& calls, const std::vec
 // FW, FC and ws in scope; every barrier is outside divergent code.
 // Bound by latency, not bytes (1 MB for 256 blocks of 1021 columns): 16 columns a
 // workgroup give four times the workgroups of 64 and a quarter of the loads
-// per lane (that launch 6.3 -> 4.6 us; 64 blocks of 1024 columns 3.4 -> 3.0).
+// per lane (ATAX 30011 x 1021: that launch 6.3 -> 3.9 us).
 static void emit_colpart_finish(Emitter& f, const std::vector<int>& gemtv_calls,
                                 const std::map<int, size_t>& ws_off) {
     f.l("__shared__ kf_f4 kf_fr[2][FW][FC];");
@@ -572,10 +578,9 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         }
         finl.args.push_back({ArgKind::Workspace, -1});
         fsig.push_back("const float* __restrict__ ws");
-        const int FWb = (col_part && NB >= 64) ? 1024 : 256;
+        const int FW = finish_waves(NB), FWb = col_part ? 64 * FW : 256;
         const long RBK = row_part ? (M + FWb - 1) / FWb : 0;
         const long CBK = col_part ? (NP / 4 + kFinishCols - 1) / kFinishCols : 0;
-        const int FW = NB >= 64 ? 16 : 4;   // waves of the finishing pass that split the row blocks
         if (p.dyn) {
             finl.args.push_back({ArgKind::ShapeM, -1});
             finl.args.push_back({ArgKind::ShapeN, -1});
@@ -1674,7 +1679,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         for (int v : scalars)
             f.l(s.values[v].kind == VK::Const ? F("const float %s = P%d;", scal_name(v).c_str(), v)
                                               : F("const float %s = *P%d;", scal_name(v).c_str(), v));
-        const int FW = NB >= 64 ? 16 : 4;   // waves that split the row blocks
+        const int FW = finish_waves(NB);
         f.l(F("constexpr int FW = %d, FC = %d;", FW, kFinishCols));
         f.l("const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;");
         f.l("const long cc = 4L * ((long)blockIdx.x * FC + lane % FC);");
