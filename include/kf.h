@@ -180,10 +180,14 @@ enum {
                                  with opts.top_k > 1 the top_k candidates by
                                  predicted plan time, and those of the predicted
                                  combination, are timed kernel by kernel (needs
-                                 opts.bind_*) and the measured times combined  */
+                                 opts.bind_*) and the measured times combined;
+                                 the combination, the best of them and the
+                                 library's own geometry then run as whole plans,
+                                 and the fastest is returned                   */
     KF_MODE_EXHAUSTIVE = 4,   /* every candidate timed kernel by kernel on
                                  opts.stream with the buffers of opts.bind_*,
-                                 the measured times combined                   */
+                                 the measured times combined, and the fastest
+                                 whole plan returned as for KF_MODE_LEARNED    */
     KF_MODE_PARTITION = 5     /* the partition given in opts.partition         */
 };
 enum {
@@ -261,8 +265,8 @@ typedef struct kf_compile_opts {
     int32_t kernel_params_len;
     /* KF_MODE_EXHAUSTIVE and KF_MODE_LEARNED with top_k > 1: once this many
      * milliseconds of wall clock have passed since timing began, no further
-     * candidate is timed and those timed so far (at least one) are combined;
-     * 0 = no limit. */
+     * candidate is timed and those timed so far (at least one) are combined,
+     * without the comparison of whole plans; 0 = no limit. */
     int32_t time_budget_ms;
     /* The timed modes' plan workspace: caller device memory, 256-byte aligned,
      * workspace_bytes long (kf_compile_workspace_bytes gives the size every
