@@ -178,7 +178,7 @@ static void emit_colpart_finish(Emitter& f, const std::vector<int>& gemtv_calls,
 // BLAS-2 kernels
 // ============================================================================
 static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
-                          const std::vector<int>& part, const MatParams& p, bool library) {
+                          const std::vector<int>& part, const MatParams& p) {
     KernelCode kc;
     kc.mat = true;
     kc.calls = calls;
@@ -188,11 +188,12 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     // E matrix elements per 16-byte load unit (4 FP32, 8 BF16, 16 FP8); a lane
     // takes p.k units per row, i.e. K = k E / 4 float4 column groups.
     const int E = kernel_unit_elems(s, calls, p.unit), EG = E / 4;
-    const int U = p.k, K = p.k * EG, W = p.waves, G = p.group, R = p.rows, NT = 64 * W;
+    const int U = p.k, K = p.k * EG, W = p.waves, G = p.group, R = p.rows, NT = 64 * W, TB = p.turns;
+    const bool pairs = p.sums == ColSum::Pairs, steps = p.sums == ColSum::Steps;
     int LG = 0;
     while ((1 << LG) < G) ++LG;
     const long C = 64L * E * U;
-    const long S = (N + C - 1) / C, NB = (M + R - 1) / R;
+    const long S = (N + C - 1) / C, NB = p.blocks > 0 ? (long)p.blocks : (M + R - 1) / R;
     const long NP = (N + 3) / 4 * 4;
 
     // ---- classify operands
@@ -295,10 +296,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         for (int v : mat_out) e.l(F("constexpr long LD%d = %ldL;", v, (long)s.values[v].ld));
     }
     e.l("const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;");
-    e.l("const long sidx = blockIdx.x % S, rb = blockIdx.x / S;");
-    // NB row blocks of equal size, at most R rows each
-    if (!p.dyn && M % NB == 0) e.l("const long c0 = sidx * C, r0 = rb * (M / NB), r1 = r0 + M / NB;");
-    else e.l("const long c0 = sidx * C, r0 = rb * M / NB, r1 = (rb + 1) * M / NB;");
+    e.l("const long sidx = blockIdx.x % S, c0 = sidx * C;");
     e.l("(void)ws;");
     for (int v : scalars) {
         if (s.values[v].kind == VK::Const) e.l(F("const float %s = P%d;", scal_name(v).c_str(), v));
@@ -313,6 +311,15 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         e.l("#pragma unroll");
         e.l(F("for (int j = 0; j < K; ++j) cv%d[j] = kf_ld4_tail(V%d, col[j], N);", v, v));
     }
+    // NB row blocks of equal size, at most R rows each; a workgroup takes TB of them in turn
+    if (TB > 1) {
+        e.l(F("for (long rb = blockIdx.x / S * %d, rb1 = rb + %d < NB ? rb + %d : NB; rb < rb1; ++rb) {", TB, TB, TB));
+        e.ind++;
+    } else {
+        e.l("const long rb = blockIdx.x / S;");
+    }
+    if (!p.dyn && M % NB == 0) e.l("const long r0 = rb * (M / NB), r1 = r0 + M / NB;");
+    else e.l("const long r0 = rb * M / NB, r1 = (rb + 1) * M / NB;");
     // row vectors staged in LDS; rows past the end read as zero
     for (int v : rowv) {
         e.l(F("__shared__ float rv%d[R];", v));
@@ -320,9 +327,9 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     }
     // cleared accumulators (Algorithm 1, "clear outputs of accumulated reductions")
     for (int c : gemtv_calls) {
-        e.l(F("kf_f4 acc%d[K];", c));
+        e.l(F(pairs ? "kf_cs4 acc%d[K];" : "kf_f4 acc%d[K];", c));
         e.l("#pragma unroll");
-        e.l(F("for (int j = 0; j < K; ++j) acc%d[j] = kf_zero4();", c));
+        e.l(F(pairs ? "for (int j = 0; j < K; ++j) acc%d[j] = kf_cs4_init(kf_zero4());" : "for (int j = 0; j < K; ++j) acc%d[j] = kf_zero4();", c));
     }
     e.l("__syncthreads();");
 
@@ -393,6 +400,8 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     };
     auto emit_compute = [&](bool edge) {
         for (int c : gemv_calls) e.l(F("float rp%d[G];", c));
+        for (int c : gemtv_calls)
+            if (pairs || steps) e.l(F("kf_f4 st%d[K];", c));
         e.l("#pragma unroll");
         e.l("for (int gi = 0; gi < G; ++gi) {");
         e.ind++;
@@ -428,7 +437,8 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
                 if (qscale >= 0) e.l(F("const float xr%d = rv%d[rl] * rv%d[rl];", c, qscale, k.in[1]));
                 else e.l(F("const float xr%d = rv%d[rl];", c, k.in[1]));
                 e.l("#pragma unroll");
-                e.l(F("for (int j = 0; j < K; ++j) acc%d[j] = kf_fma4s(xr%d, %s[j], acc%d[j]);", c, c, Min.c_str(), c));
+                if (pairs || steps) e.l(F("for (int j = 0; j < K; ++j) st%d[j] = gi == 0 ? kf_mul4s(xr%d, %s[j]) : kf_fma4s(xr%d, %s[j], st%d[j]);", c, c, Min.c_str(), c, Min.c_str(), c));
+                else e.l(F("for (int j = 0; j < K; ++j) acc%d[j] = kf_fma4s(xr%d, %s[j], acc%d[j]);", c, c, Min.c_str(), c));
             } else if (k.op == Op::Gemv) {
                 e.l(F("const float t%d = kf_dotk<K>(%s, cv%d);", c, Min.c_str(), k.in[1]));
                 if (qscale >= 0) e.l(F("rp%d[gi] = rv%d[rl] * t%d;", c, qscale, c));
@@ -437,6 +447,13 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         }
         e.ind--;
         e.l("}");
+        // the step's column sums
+        for (int c : gemtv_calls) {
+            if (!pairs && !steps) break;
+            e.l("#pragma unroll");
+            e.l(pairs ? F("for (int j = 0; j < K; ++j) acc%d[j] = kf_cs4_add(acc%d[j], st%d[j]);", c, c, c)
+                      : F("for (int j = 0; j < K; ++j) acc%d[j] += st%d[j];", c, c));
+        }
         // row reductions of this group
         if (!gemv_calls.empty()) {
             for (int c : gemv_calls) e.l(F("const float sum%d = kf_rows_reduce<LG>(rp%d);", c, c));
@@ -458,31 +475,13 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         }
     };
     e.l("const bool cols_in = c0 + C <= N;");
-    // long row ranges of the library's own geometry: a wave's column sums enter a
-    // (sum, error) pair every FL rows, which keeps the plain FP32 chains short
-    // whatever the block's length. A requested point keeps the registers for its own
-    // loads (BiCGK of BF16 16384 x 16384 with 2048 rows: 491 us with pairs, 201 without).
-    const int FL = 128;
-    const bool flush = library && !gemtv_calls.empty() && R > W * FL;
-    if (flush) {
-        for (int c : gemtv_calls) {
-            e.l(F("kf_cs4 tot%d[K];", c));
-            e.l("#pragma unroll");
-            e.l(F("for (int j = 0; j < K; ++j) tot%d[j] = kf_cs4_init(kf_zero4());", c));
-        }
-        e.l(F("for (long h0 = r0; h0 < r1; h0 += W * %d) {", FL));
-        e.ind++;
-        e.l(F("const long h1 = h0 + W * %d < r1 ? h0 + W * %d : r1;", FL, FL));
-    } else {
-        e.l("const long h0 = r0, h1 = r1;");
-    }
     // whole groups first, in a loop without edge code, which the compiler
     // pipelines (BiCGK n = 16384 with two rows of one float4 per step: 199 us with the
     // edge test in the loop, 161 without); then what is left of the range
-    e.l("long g0 = h0 + (long)wave * G;");
+    e.l("long g0 = r0 + (long)wave * G;");
     e.l("if (cols_in) {");
     e.ind++;
-    e.l("for (; g0 + G <= h1; g0 += (long)W * G) {");
+    e.l("for (; g0 + G <= r1; g0 += (long)W * G) {");
     e.ind++;
     emit_loads(false);
     emit_compute(false);
@@ -490,33 +489,25 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     e.l("}");
     e.ind--;
     e.l("}");
-    e.l("for (; g0 < h1; g0 += (long)W * G) {");
+    e.l("for (; g0 < r1; g0 += (long)W * G) {");
     e.ind++;
     emit_loads(true);
     emit_compute(true);
     e.ind--;
     e.l("}");
-    if (flush) {
-        for (int c : gemtv_calls) {
-            e.l("#pragma unroll");
-            e.l(F("for (int j = 0; j < K; ++j) { tot%d[j] = kf_cs4_add(tot%d[j], acc%d[j]); acc%d[j] = kf_zero4(); }", c, c, c, c));
-        }
-        e.ind--;
-        e.l("}");
-        for (int c : gemtv_calls) {
-            e.l("#pragma unroll");
-            e.l(F("for (int j = 0; j < K; ++j) acc%d[j] = kf_cs4_value(tot%d[j]);", c, c));
-        }
-    }
 
     // column reductions: merge the waves in wave order through LDS
     if (!gemtv_calls.empty()) {
         const int ngt = (int)gemtv_calls.size();
-        e.l(F("__shared__ kf_f4 kf_red[%d][W * (C / 4)];", ngt));
+        e.l(F("__shared__ kf_f4 kf_red[%d][%d][W * (C / 4)];", ngt, pairs ? 2 : 1));
         for (int i = 0; i < ngt; ++i) {
             int c = gemtv_calls[i];
             e.l("#pragma unroll");
-            e.l(F("for (int j = 0; j < K; ++j) kf_red[%d][wave * (C / 4) + (int)((col[j] - c0) >> 2)] = acc%d[j];", i, c));
+            e.l("for (int j = 0; j < K; ++j) {");
+            e.l("  const int q = wave * (C / 4) + (int)((col[j] - c0) >> 2);");
+            if (pairs) e.l(F("  kf_red[%d][0][q] = acc%d[j].s; kf_red[%d][1][q] = acc%d[j].c;", i, c, i, c));
+            else e.l(F("  kf_red[%d][0][q] = acc%d[j];", i, c));
+            e.l("}");
         }
         e.l("__syncthreads();");
         e.l("for (int q = tid; q < C / 4; q += NT) {");
@@ -524,8 +515,13 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         e.l("const long cc = c0 + 4L * q;");
         for (int i = 0; i < ngt; ++i) {
             int c = gemtv_calls[i];
-            e.l(F("kf_cs4 cs%d = kf_cs4_init(kf_red[%d][q]);", c, i));
-            e.l(F("for (int w = 1; w < W; ++w) cs%d = kf_cs4_add(cs%d, kf_red[%d][w * (C / 4) + q]);", c, c, i));
+            if (pairs) {
+                e.l(F("kf_cs4 cs%d = {kf_red[%d][0][q], kf_red[%d][1][q]};", c, i, i));
+                e.l(F("for (int w = 1; w < W; ++w) { const kf_cs4 o = {kf_red[%d][0][w * (C / 4) + q], kf_red[%d][1][w * (C / 4) + q]}; cs%d = kf_cs4_merge(cs%d, o); }", i, i, c, c));
+            } else {
+                e.l(F("kf_cs4 cs%d = kf_cs4_init(kf_red[%d][0][q]);", c, i));
+                e.l(F("for (int w = 1; w < W; ++w) cs%d = kf_cs4_add(cs%d, kf_red[%d][0][w * (C / 4) + q]);", c, c, i));
+            }
             e.l(F("const kf_f4 sum%d = kf_cs4_value(cs%d);", c, c));
         }
         if (!col_part) {
@@ -550,6 +546,11 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
             for (int c : gemtv_calls) e.l(F("  kf_st4(ws + %zuL + rb * NP + cc, sum%d);", ws_off[c], c));
             e.l("}");
         }
+        e.ind--;
+        e.l("}");
+    }
+    if (TB > 1) {
+        e.l("__syncthreads();");   // the LDS is written again by the next block
         e.ind--;
         e.l("}");
     }
@@ -674,12 +675,12 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     head << "extern \"C\" __global__ void __launch_bounds__(" << NT << ") " << kc.name << "(\n"
          << sigs << ") {\n" << e.o.str() << "}\n";
     mainl.name = kc.name;
-    mainl.grid = (int)(S * NB);
+    mainl.grid = (int)(S * ((NB + TB - 1) / TB));
     mainl.block = NT;
     if (p.dyn) {
         mainl.dyn_grid = 1;
         mainl.dyn_c = C;
-        mainl.dyn_r = R;
+        mainl.dyn_r = R * TB;
     }
     kc.launches.push_back(mainl);
     if (row_part || col_part) {
@@ -689,9 +690,9 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         kc.launches.push_back(finl);
     }
     kc.source = head.str();
-    kc.lds_bytes = 16 + rowv.size() * (size_t)R * 4 + gemtv_calls.size() * (size_t)W * (C / 4) * 16;
-    kc.params_json = F("{\"k\": %d, \"waves\": %d, \"group\": %d, \"rows\": %d, \"unit_elems\": %d, \"strips\": %ld, \"row_blocks\": %ld}",
-                       U, W, G, R, E, S, NB);
+    kc.lds_bytes = 16 + rowv.size() * (size_t)R * 4 + gemtv_calls.size() * (size_t)W * (pairs ? 2 : 1) * (C / 4) * 16;
+    kc.params_json = F("{\"k\": %d, \"waves\": %d, \"group\": %d, \"rows\": %d, \"column_sums\": \"%s\", \"turns\": %d, \"unit_elems\": %d, \"strips\": %ld, \"row_blocks\": %ld}",
+                       U, W, G, R, pairs ? "pairs" : steps ? "steps" : "rows", TB, E, S, NB);
     kernel_bytes(s, calls, part, &kc.bytes_read, &kc.bytes_written);
     return kc;
 }
@@ -1766,7 +1767,7 @@ KernelCode generate_kernel(const Script& s, const std::vector<int>& calls,
         if (sp.mat) {
             MatParams q = kernel_mat_params(s, calls, mp);
             q.dyn = mp.dyn;
-            kc = is_stream(s, calls, mp) ? gen_mat_stream(s, calls, part, q) : gen_mat(s, calls, part, q, library_geometry(mp));
+            kc = is_stream(s, calls, mp) ? gen_mat_stream(s, calls, part, q) : gen_mat(s, calls, part, q);
         } else {
             kc = gen_vec(s, calls, part, default_vec_params(sp.a, vp));
         }

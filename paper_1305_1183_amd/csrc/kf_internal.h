@@ -78,8 +78,19 @@ std::vector<std::vector<int>> kernels_in_order(const Script& s, const std::vecto
 
 // ---- implementation parameters ---------------------------------------------
 // sched 1 = row-resident; dyn: rows, cols and leading dimensions are kernel
-// arguments (a plan compiled with KF_COMPILE_RUNTIME_SHAPE), not constants
-struct MatParams { int k = 0, waves = 0, group = 0, rows = 0, sched = 0, unit = 0; bool dyn = false; };
+// arguments (a plan compiled with KF_COMPILE_RUNTIME_SHAPE), not constants. Derived,
+// for strip kernels in the library's geometry: how a wave adds its rows of a column
+// (row by row in FP32; the sum of each step's rows in FP32; that sum into a (sum,
+// error) pair), turns, the row blocks that a workgroup takes one after another, and
+// then blocks, their number (0: as `rows` gives it)
+enum class ColSum { Plain, Steps, Pairs };
+struct MatParams {
+    int k = 0, waves = 0, group = 0, rows = 0, sched = 0, unit = 0;
+    bool dyn = false;
+    ColSum sums = ColSum::Plain;
+    int turns = 1;
+    int64_t blocks = 0;
+};
 struct VecParams { int unroll = 0, threads = 0, grid = 0; };
 // e_per_unit: matrix elements per 16-byte load unit of the kernel (4 for FP32,
 // 8 with a BF16 matrix, 16 with an FP8 matrix).

@@ -331,25 +331,65 @@ MatParams default_mat_params(int64_t rows, int64_t cols, const MatParams& req, i
 //  - other FP32 kernels: one workgroup of sixteen waves per CU, 2 KiB strips. BiCGK
 //    n = 16384 165 (2048 workgroups of four waves: 186), 5003 21.3 (26.5), 12001 94
 //    (124), 700 x 16000 12.5 (22.6).
-//  - BF16 and FP8 in 16-byte units: three workgroups of eight waves per CU hide the
-//    conversion. BiCGK FP8 n = 16384 52 (77), BF16 85 (101). One or two strips leave
-//    row blocks only; sixteen waves a workgroup then halve their number
-//    (FP8 20000 x 700 15.4, 21 with eight).
-static MatParams library_mat_params(int64_t rows, int64_t cols, int E, bool stores) {
+//  - BF16 and FP8 in 16-byte units: 24 and 20 waves per CU, as many as their registers
+//    allow, hide the conversion. BiCGK n = 16384 FP8 54 (79), BF16 90 (96). One or two
+//    strips leave row blocks only; sixteen waves a workgroup then keep their number down
+//    (FP8 50000 x 500 21, 50).
+// The number of workgroups stays within one round of the chip: a few more would run in
+// a second, nearly empty one (BiCGK n = 10007 98 with 260 workgroups, 66 with 240; n =
+// 24000 493 with 282, 354 with 235).
+//
+// A wave adds its rows of a column in plain FP32 before (sum, error) pairs take over:
+// no longer chains of them than in the small workgroups (default_mat_params, `chain`
+// rows), so that larger blocks do not cost precision. Past that, in this order:
+//  - steps of two or four rows enter pairs one by one, where the registers are there
+//    (GEMVER n = 16384 509 us, 511 in plain FP32);
+//  - a step's rows are summed first, which halves the chain (BiCGK 20000 x 700 17.7 us,
+//    18.0 with one row a step): 1.5 + n / 4 squared roundings a row over n rows instead
+//    of (n + 1) / 2;
+//  - a workgroup takes its rows in several blocks, one after another, each with its own
+//    partials, and no more of them than the small workgroups have (BiCGK n = 32768 666
+//    us, 688 with pairs every 128 rows; FP8 178 and 258). So do blocks of more than 4096
+//    rows, whose vectors are staged in LDS (GEMVER n = 24000 1230 us; 1500 with 282
+//    workgroups of one block each).
+static MatParams library_mat_params(int64_t rows, int64_t cols, int E, bool stores, bool column_sums) {
     MatParams p;
+    const int64_t few = default_mat_params(rows, cols, MatParams(), E).rows, chain = few / 4;
+    const int64_t by_row = chain + chain / 16, by_step = (11 * chain - 17) / 5;   // rows of a wave, within 5% of its error
     int per_cu;
-    const bool small = (double)rows * (double)cols <= 6e6;
+    const bool small = (double)rows * (double)cols <= 6e6, general = !small && !stores;
     if (small) { p.k = 1; p.waves = 8; p.group = 4; per_cu = 16; }
     else if (stores) { const bool line = cols % 256 == 0; p.k = line ? 1 : 2; p.waves = 8; p.group = line ? 4 : 2; per_cu = 8; }
     else if (E == 4) { p.k = 2; p.waves = 16; p.group = 1; per_cu = 16; }
-    else if (cols <= 2 * 64 * E) { p.k = 1; p.waves = 16; p.group = 1; per_cu = 16; }
-    else { p.k = 1; p.waves = 8; p.group = 1; per_cu = 24; }
-    const int64_t C = 64LL * E * p.k, S = (cols + C - 1) / C, unit = p.waves * p.group;
-    const int64_t nb = std::max<int64_t>(1, 256 * per_cu / (S * p.waves));
-    int64_t r = (rows + nb - 1) / nb;
-    r = std::max<int64_t>((r + unit - 1) / unit * unit, p.waves * std::max(4, p.group));
-    // the row vectors of a block are staged in LDS
-    p.rows = (int)std::min<int64_t>(r, 4096 / unit * unit);
+    else if (cols <= 2 * 64 * E) { p.k = 1; p.waves = 16; p.group = 2; per_cu = 16; }
+    else { p.k = 1; p.waves = 4; p.group = 2; per_cu = E == 16 ? 20 : 24; }
+    const int64_t C = 64LL * E * p.k, S = (cols + C - 1) / C, nb = std::max<int64_t>(1, 256 * per_cu / (S * p.waves));
+    auto block_rows = [&](int64_t n) {   // rows of each of n blocks, whole steps
+        const int64_t r = (rows + n - 1) / n, unit = p.waves * p.group;
+        return std::max<int64_t>((r + unit - 1) / unit * unit, p.waves * std::max(4, p.group));
+    };
+    int64_t r = block_rows(nb);
+    auto wave_rows = [&]() { return (r + p.waves - 1) / p.waves; };
+    if (column_sums && general && E == 4 && wave_rows() > by_row && wave_rows() <= by_step) {
+        p.group = 2;
+        r = block_rows(nb);
+    }
+    int64_t most = 4096;
+    if (!column_sums) {
+    } else if (general && p.group > 1) {
+        p.sums = ColSum::Steps;
+        most = std::min(most, by_step * p.waves);
+    } else if (p.group == 1) {
+        most = std::min(most, by_row * p.waves);
+    } else if (wave_rows() > chain) {
+        p.sums = ColSum::Pairs;
+    }
+    if (r > most) {
+        p.turns = (int)((r + most - 1) / most);
+        p.blocks = std::min(nb * p.turns, (rows + few - 1) / few);
+        r = block_rows(p.blocks);
+    }
+    p.rows = (int)r;
     return p;
 }
 
@@ -358,7 +398,6 @@ bool library_geometry(const MatParams& p) { return p.sched == 0 && p.k <= 0 && p
 MatParams kernel_mat_params(const Script& s, const std::vector<int>& calls, const MatParams& req) {
     const Space sp = call_space(s, calls[0]);
     const int E = kernel_unit_elems(s, calls, req.unit);
-    if (!library_geometry(req)) return default_mat_params(sp.a, sp.b, req, E);
     const std::set<int> mine(calls.begin(), calls.end());
     std::set<int> mats, cols, rows;
     int gemtv = 0;
@@ -380,18 +419,25 @@ MatParams kernel_mat_params(const Script& s, const std::vector<int>& calls, cons
         stores = stores || o.output;
         for (int d : o.consumers) stores = stores || !mine.count(d);
     }
-    MatParams p = library_mat_params(sp.a, sp.b, E, stores);
-    p.unit = req.unit;
+    MatParams p = library_mat_params(sp.a, sp.b, E, stores, gemtv > 0);
     // kernels of so many operands that a lane's rows, vectors and accumulators
     // outgrow the registers (128 with sixteen waves in a workgroup, 256 with
     // eight) or the staged vectors and wave sums the LDS keep the small workgroups
-    const int K = p.k * E / 4;
-    const int regs = 4 * K * (p.group * (int)mats.size() + (int)cols.size() + gemtv + (ger ? 1 : 0));
-    const int64_t lds = (int64_t)rows.size() * p.rows * 4 + (int64_t)gemtv * p.waves * 64 * K * 16;
-    if (regs > (p.waves > 8 ? 72 : 168) || lds > 72 * 1024) {
-        p = default_mat_params(sp.a, sp.b, req, E);
+    const int K = p.k * E / 4, sets = p.sums == ColSum::Pairs ? 3 : 1;
+    const int regs = 4 * K * (p.group * (int)mats.size() + (int)cols.size() + gemtv * sets + (ger ? 1 : 0));
+    const int64_t lds = (int64_t)rows.size() * p.rows * 4 + (int64_t)gemtv * p.waves * std::min(sets, 2) * 64 * K * 16;
+    // (kernels that store a matrix have one workgroup on a CU, the others two)
+    if (regs > (p.waves > 8 ? 72 : 168) || lds > (stores ? 112 : 72) * 1024) p = default_mat_params(sp.a, sp.b, MatParams(), E);
+    p.unit = req.unit;
+    if (library_geometry(req)) return p;
+    // a requested point that is the library's own gives the library's kernel
+    MatParams q = default_mat_params(sp.a, sp.b, req, E);
+    if (q.k == p.k && q.waves == p.waves && q.group == p.group && q.rows == p.rows) {
+        q.sums = p.sums;
+        q.turns = p.turns;
+        q.blocks = p.blocks;
     }
-    return p;
+    return q;
 }
 
 VecParams default_vec_params(int64_t n, const VecParams& req) {
