@@ -213,9 +213,11 @@ typedef struct kf_compile_opts {
      * per workgroup (multiple of mat_waves*mat_group). vec_unroll: float4 per
      * thread per step (1, 2, 4, 8); vec_threads: 64..1024; vec_grid: max
      * workgroups (grid-stride beyond). With no mat_* parameter requested, a
-     * kernel whose reductions are all gemv streams whole rows instead of column
-     * strips ("row-stream" in kf_plan_describe): same strips and bits, no
-     * partial sums in HBM. */
+     * kernel whose reductions are all gemv (of at most six matrices and column
+     * vectors together) streams whole rows instead of column strips
+     * ("row-stream" in kf_plan_describe): no partial sums in HBM, and the same
+     * bits as the strip kernel that fuses the gemv with a gemtv, if both load
+     * units of one size and the strip kernel is in the library's geometry too. */
     int32_t mat_k, mat_waves, mat_group, mat_rows;
     int32_t vec_unroll, vec_threads, vec_grid;
     /* BLAS-2 schedule: 0 = column strips x row blocks (mat_k used), 1 = row-

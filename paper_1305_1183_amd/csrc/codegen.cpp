@@ -132,6 +132,11 @@ void kernel_bytes(const Script& s, const std::vector<int>& calls, const std::vec
 // eight 3.9).
 static int finish_waves(long NB) { return NB > 128 ? 8 : 4; }
 
+// Chains in which the partial sums of a row are added before they are merged: as many
+// as a wave that streams a row has strips in flight, so that strip and row-stream kernels
+// merge alike (one chain of 258 strips is 11 us of dependent additions).
+static int row_chains(int E) { return E == 4 ? 8 : 2; }
+
 // Finishing launch of column partials (both BLAS-2 schedules): a workgroup takes
 // FC float4 columns, and the 64 / FC lane groups of its FW waves split the row
 // blocks. Group gid adds blocks gid, gid + FWG, ... of each gemtv call's partials at
@@ -190,10 +195,13 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     const int E = kernel_unit_elems(s, calls, p.unit), EG = E / 4;
     const int U = p.k, K = p.k * EG, W = p.waves, G = p.group, R = p.rows, NT = 64 * W, TB = p.turns;
     const bool pairs = p.sums == ColSum::Pairs, steps = p.sums == ColSum::Steps;
+    // Row sums end every CR columns and meet as pairs: the strip, or each 64 E of its
+    // columns in the library's geometry, so that wider strips do not cost precision
+    const int SUB = p.sub;
     int LG = 0;
-    while ((1 << LG) < G) ++LG;
-    const long C = 64L * E * U;
-    const long S = (N + C - 1) / C, NB = p.blocks > 0 ? (long)p.blocks : (M + R - 1) / R;
+    while ((1 << LG) < G * SUB) ++LG;
+    const long C = 64L * E * U, CR = C / SUB;
+    const long S = (N + C - 1) / C, SR = (N + CR - 1) / CR, NB = p.blocks > 0 ? (long)p.blocks : (M + R - 1) / R;
     const long NP = (N + 3) / 4 * 4;
 
     // ---- classify operands
@@ -227,14 +235,14 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         if (s.values[v].scale >= 0) push_u(rowv, s.values[v].scale);
     for (int v : colv) push_u(vec_in, v);
     for (int v : rowv) push_u(vec_in, v);
-    const bool row_part = !gemv_calls.empty() && S > 1;
+    const bool row_part = !gemv_calls.empty() && SR > 1;
     const bool col_part = !gemtv_calls.empty() && NB > 1;
 
     // ---- workspace layout (floats) and tickets
     std::map<int, size_t> ws_off;
     size_t wsz = 0;
     if (row_part)
-        for (int c : gemv_calls) { ws_off[c] = wsz; wsz += (size_t)S * M; wsz = (wsz + 3) / 4 * 4; }
+        for (int c : gemv_calls) { ws_off[c] = wsz; wsz += (size_t)SR * M; wsz = (wsz + 3) / 4 * 4; }
     if (col_part)
         for (int c : gemtv_calls) { ws_off[c] = wsz; wsz += (size_t)NB * NP; }
     kc.ws_floats = wsz;
@@ -285,13 +293,13 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
 
     // ---- body
     Emitter e;
-    e.l(F("constexpr int K = %d, W = %d, G = %d, LG = %d, R = %d, NT = %d, E = %d, EG = %d;", K, W, G, LG, R, NT, E, EG));
+    e.l(F("constexpr int K = %d, W = %d, G = %d, LG = %d, R = %d, NT = %d, E = %d, EG = %d, SUB = %d;", K, W, G, LG, R, NT, E, EG, SUB));
     if (p.dyn) {
         e.l(F("constexpr long C = %ldL;", C));
-        e.l("const long M = M_, N = N_, S = (N + C - 1) / C, NB = (M + R - 1) / R, NP = (N + 3) / 4 * 4;");
-        e.l("(void)NB; (void)NP;");
+        e.l("const long M = M_, N = N_, S = (N + C - 1) / C, SR = (N + C / SUB - 1) / (C / SUB), NB = (M + R - 1) / R, NP = (N + 3) / 4 * 4;");
+        e.l("(void)NB; (void)NP; (void)SR;");
     } else {
-        e.l(F("constexpr long M = %ldL, N = %ldL, C = %ldL, S = %ldL, NB = %ldL, NP = %ldL;", M, N, C, S, NB, NP));
+        e.l(F("constexpr long M = %ldL, N = %ldL, C = %ldL, S = %ldL, SR = %ldL, NB = %ldL, NP = %ldL;", M, N, C, S, SR, NB, NP));
         for (int v : mat_in) e.l(F("constexpr long LD%d = %ldL;", v, (long)s.values[v].ld));
         for (int v : mat_out) e.l(F("constexpr long LD%d = %ldL;", v, (long)s.values[v].ld));
     }
@@ -399,7 +407,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         e.l("}");
     };
     auto emit_compute = [&](bool edge) {
-        for (int c : gemv_calls) e.l(F("float rp%d[G];", c));
+        for (int c : gemv_calls) e.l(F("float rp%d[G * SUB];", c));
         for (int c : gemtv_calls)
             if (pairs || steps) e.l(F("kf_f4 st%d[K];", c));
         e.l("#pragma unroll");
@@ -440,9 +448,10 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
                 if (pairs || steps) e.l(F("for (int j = 0; j < K; ++j) st%d[j] = gi == 0 ? kf_mul4s(xr%d, %s[j]) : kf_fma4s(xr%d, %s[j], st%d[j]);", c, c, Min.c_str(), c, Min.c_str(), c));
                 else e.l(F("for (int j = 0; j < K; ++j) acc%d[j] = kf_fma4s(xr%d, %s[j], acc%d[j]);", c, c, Min.c_str(), c));
             } else if (k.op == Op::Gemv) {
-                e.l(F("const float t%d = kf_dotk<K>(%s, cv%d);", c, Min.c_str(), k.in[1]));
-                if (qscale >= 0) e.l(F("rp%d[gi] = rv%d[rl] * t%d;", c, qscale, c));
-                else e.l(F("rp%d[gi] = t%d;", c, c));
+                for (int u = 0; u < SUB; ++u) {
+                    const std::string t = F("kf_dotk<K / SUB>(%s + %d * (K / SUB), cv%d + %d * (K / SUB))", Min.c_str(), u, k.in[1], u);
+                    e.l(F("rp%d[gi * SUB + %d] = ", c, u) + (qscale >= 0 ? F("rv%d[rl] * ", qscale) : "") + t + ";");
+                }
             }
         }
         e.ind--;
@@ -459,14 +468,17 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
             for (int c : gemv_calls) e.l(F("const float sum%d = kf_rows_reduce<LG>(rp%d);", c, c));
             e.l("{");
             e.ind++;
-            e.l("const long row = g0 + (lane >> (6 - LG));");
-            if (edge) e.l("if ((lane & ((64 >> LG) - 1)) == 0 && row < r1) {");
-            else e.l("if ((lane & ((64 >> LG) - 1)) == 0) {");
+            e.l("const long row = g0 + (lane >> (6 - LG)) / SUB;");
+            // the strip's part that this lane holds; a row of one part has it in part 0
+            if (SUB > 1) e.l("const long part = sidx * SUB + (lane >> (6 - LG)) % SUB;");
+            else e.l("const long part = sidx;");
+            e.l("(void)part;");
+            e.l(F("if ((lane & ((64 >> LG) - 1)) == 0%s%s) {", edge ? " && row < r1" : "", SUB > 1 && (p.dyn || S * SUB != SR) ? " && part < SR" : ""));
             e.ind++;
             if (!row_part) {
                 row_epilogue("row");
             } else {
-                for (int c : gemv_calls) e.l(F("ws[%zuL + sidx * M + row] = sum%d;", ws_off[c], c));
+                for (int c : gemv_calls) e.l(F("ws[%zuL + part * M + row] = sum%d;", ws_off[c], c));
             }
             e.ind--;
             e.l("}");
@@ -587,12 +599,12 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
             finl.args.push_back({ArgKind::ShapeN, -1});
             fsig.push_back("long M_");
             fsig.push_back("long N_");
-            f.l(F("constexpr long C = %ldL, R = %dL, FWB = %dL;", C, R, FWb));
-            f.l("const long M = M_, N = N_, S = (N + C - 1) / C, NB = (M + R - 1) / R, NP = (N + 3) / 4 * 4;");
+            f.l(F("constexpr long R = %dL, FWB = %dL; (void)FWB;", R, FWb));
+            f.l(F("const long M = M_, N = N_, SR = (N + %ldL) / %ldL, NB = (M + R - 1) / R, NP = (N + 3) / 4 * 4;", CR - 1, CR));
             f.l(row_part ? "const long RBK = (M + FWB - 1) / FWB;" : "const long RBK = 0;");
-            f.l("(void)S; (void)NB; (void)NP; (void)RBK;");
+            f.l("(void)SR; (void)NB; (void)NP; (void)RBK;");
         } else {
-            f.l(F("constexpr long M = %ldL, N = %ldL, S = %ldL, NB = %ldL, NP = %ldL, RBK = %ldL;", M, N, S, NB, NP, RBK));
+            f.l(F("constexpr long M = %ldL, N = %ldL, SR = %ldL, NB = %ldL, NP = %ldL, RBK = %ldL;", M, N, SR, NB, NP, RBK));
         }
         f.l(F("constexpr int FW = %d, FC = %d; (void)FW; (void)FC;", FW, kFinishCols));
         for (int v : scalars) {
@@ -605,12 +617,9 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
             f.l("const long row = (long)blockIdx.x * blockDim.x + threadIdx.x;");
             f.l("if (row < M) {");
             f.ind++;
-            // the S strip partials of a row, compensated, in strip order
-            for (int c : gemv_calls) {
-                f.l(F("kf_cs cs%d = kf_cs_init(ws[%zuL + row]);", c, ws_off[c]));
-                f.l(F("for (long si = 1; si < S; ++si) cs%d = kf_cs_add(cs%d, ws[%zuL + si * M + row]);", c, c, ws_off[c]));
-                f.l(F("const float sum%d = kf_cs_value(cs%d);", c, c));
-            }
+            // the SR partial sums of a row, compensated
+            for (int c : gemv_calls)
+                f.l(F("const float sum%d = kf_cs_value(kf_sum_parts<%d>(SR, [&](long si) { return ws[%zuL + si * M + row]; }));", c, row_chains(E), ws_off[c]));
             for (int c : gemv_calls) {
                 const Call& k = s.calls[c];
                 std::string val = F("%s * sum%d", scal_name(k.alpha).c_str(), c);
@@ -691,8 +700,8 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     }
     kc.source = head.str();
     kc.lds_bytes = 16 + rowv.size() * (size_t)R * 4 + gemtv_calls.size() * (size_t)W * (pairs ? 2 : 1) * (C / 4) * 16;
-    kc.params_json = F("{\"k\": %d, \"waves\": %d, \"group\": %d, \"rows\": %d, \"column_sums\": \"%s\", \"turns\": %d, \"unit_elems\": %d, \"strips\": %ld, \"row_blocks\": %ld}",
-                       U, W, G, R, pairs ? "pairs" : steps ? "steps" : "rows", TB, E, S, NB);
+    kc.params_json = F("{\"k\": %d, \"waves\": %d, \"group\": %d, \"rows\": %d, \"column_sums\": \"%s\", \"turns\": %d, \"unit_elems\": %d, \"strips\": %ld, \"row_sums\": %ld, \"row_blocks\": %ld}",
+                       U, W, G, R, pairs ? "pairs" : steps ? "steps" : "rows", TB, E, S, SR, NB);
     kernel_bytes(s, calls, part, &kc.bytes_read, &kc.bytes_written);
     return kc;
 }
@@ -704,15 +713,16 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
 // nothing ties a workgroup to a column strip: a wave walks a row strip by strip
 // and finishes its dot itself. Against the strip kernels this saves the partial
 // sums in HBM and the finishing launch; against the row-resident schedule, the
-// barrier per row group. The strips, their sums and the compensated merge in
-// strip order are those of the strip kernels of the same shape, so a gemv gives
-// the same bits alone as fused with a gemtv.
+// barrier per row group. The strips of 64 E columns, their sums and the compensated
+// merge in column order are those of the strip kernels in the library's geometry, so
+// a gemv gives the same bits alone as fused with a gemtv.
 //
-// U strips are in flight per row and step. Where whole rows would leave the chip
-// short of waves, CWV waves share a row (strips cw, cw + CWV, ... in steps); the
-// strip sums then meet in LDS and one lane per row merges them.
+// U strips are in flight per row and step, and lane group u of the wave keeps the pair
+// of strips u, u + U, .... Where whole rows would leave the chip short of waves, CWV
+// waves share a row (strips cw, cw + CWV, ... in steps); the strip sums then meet in LDS
+// and as many lanes per row take them up. Either way the pairs are merged by a butterfly.
 struct StreamGeom { int W, G, U, CWV; };
-static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E, int K);
+static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E);
 
 static bool is_stream(const Script& s, const std::vector<int>& calls, const MatParams& p) {
     if (!library_geometry(p)) return false;
@@ -740,8 +750,7 @@ static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls,
     const Space sp = call_space(s, calls[0]);
     const long M = (long)sp.a, N = (long)sp.b;
     const int E = kernel_unit_elems(s, calls, p.unit), EG = E / 4;
-    // K float4 groups per lane and strip, as in the strip kernels
-    const int KU = p.k, K = KU * EG;
+    const int K = EG;   // float4 groups per lane and strip
 
     std::vector<int> mat_in, mat_out, colv, rowv, vec_in, vec_out, gemv_calls, scalars;
     auto push_u = [](std::vector<int>& v, int x) {
@@ -765,10 +774,10 @@ static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls,
         if (s.values[v].scale >= 0) push_u(rowv, s.values[v].scale);
     for (int v : colv) push_u(vec_in, v);
     for (int v : rowv) push_u(vec_in, v);
-    StreamGeom geo = stream_geometry(M, N, E, KU);
-    if (gemv_calls.size() * (size_t)(geo.W / geo.CWV) * geo.G * ((N + 64L * E * KU - 1) / (64L * E * KU)) * 4 > 32 * 1024) geo.CWV = 1;
+    StreamGeom geo = stream_geometry(M, N, E);
+    if (gemv_calls.size() * (size_t)(geo.W / geo.CWV) * geo.G * ((N + 64L * E - 1) / (64L * E)) * 4 > 32 * 1024) geo.CWV = 1;
     const int W = geo.W, G = geo.G, U = geo.U, CWV = geo.CWV, T = W / CWV, NT = 64 * W;
-    const long S = (N + 64L * E * KU - 1) / (64L * E * KU);
+    const long S = (N + 64L * E - 1) / (64L * E);
     int LGU = 0;
     while ((1 << LGU) < G * U) ++LGU;
     const bool off32 = N < (1L << 28);   // byte offsets inside a row fit 32 bits
@@ -803,9 +812,9 @@ static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls,
     Emitter e;
     e.l(F("constexpr int W = %d, G = %d, U = %d, LGU = %d, CWV = %d, T = %d, E = %d, EG = %d, K = %d;", W, G, U, LGU, CWV, T, E, EG, K));
     if (p.dyn) {
-        e.l(F("constexpr long C = %dL, SMAX = %ldL; const long M = M_, N = N_, S = (N + C - 1) / C;", 64 * E * KU, S));
+        e.l(F("constexpr long C = %dL, SMAX = %ldL; const long M = M_, N = N_, S = (N + C - 1) / C;", 64 * E, S));
     } else {
-        e.l(F("constexpr long M = %ldL, N = %ldL, C = %dL, S = %ldL, SMAX = S;", M, N, 64 * E * KU, S));
+        e.l(F("constexpr long M = %ldL, N = %ldL, C = %dL, S = %ldL, SMAX = S;", M, N, 64 * E, S));
         for (int v : mat_in) e.l(F("constexpr long LD%d = %ldL;", v, (long)s.values[v].ld));
         for (int v : mat_out) e.l(F("constexpr long LD%d = %ldL;", v, (long)s.values[v].ld));
     }
@@ -833,11 +842,7 @@ static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls,
     if (CWV > 1) {
         e.l(F("__shared__ float kf_part[%d][T][G][SMAX];", ngv));
     } else {
-        for (int c : gemv_calls) {
-            e.l(F("kf_cs ac%d[G];", c));
-            e.l("#pragma unroll");
-            e.l(F("for (int gi = 0; gi < G; ++gi) ac%d[gi] = kf_cs_init(0.f);", c));
-        }
+        for (int c : gemv_calls) e.l(F("kf_cs ac%d = kf_cs_init(0.f);", c));
     }
     const char* off = off32 ? "unsigned" : "long";
     auto emit_step = [&](bool edge) {
@@ -926,11 +931,8 @@ static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls,
                 e.l("{ const int i = lane >> (6 - LGU); const long si = c + (i % U) * CWV;");
                 e.l(F("  if ((lane & ((64 >> LGU) - 1)) == 0%s) kf_part[%d][team][i / U][si] = ss%d; }", edge ? " && si < S" : "", i, c));
             } else {
-                e.l("#pragma unroll");
-                e.l("for (int gi = 0; gi < G; ++gi)");
-                e.l("#pragma unroll");
-                e.l(F("for (int u = 0; u < U; ++u)%s ac%d[gi] = kf_cs_add(ac%d[gi], kf_lane_bcast(ss%d, (gi * U + u) << (6 - LGU)));",
-                      edge ? " if (c + u < S)" : "", c, c, c));
+                e.l(edge ? F("ac%d = kf_cs_add(ac%d, c + ((lane >> (6 - LGU)) & (U - 1)) < S ? ss%d : 0.f);", c, c, c)
+                         : F("ac%d = kf_cs_add(ac%d, ss%d);", c, c, c));
             }
         }
     };
@@ -947,28 +949,28 @@ static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls,
     e.l("}");
     e.ind--;
     e.l("}");
-    // the row's sum in lane gi of the wave (of the first wave, where waves share rows)
+    // row gi's sum in lanes gi LPR, ... of the wave (of the first wave, where waves share rows)
     if (CWV > 1) {
         e.l("__syncthreads();");
         e.l("if (cw != 0) return;");
+        e.l(F("constexpr int P = %d, LPR = P;", row_chains(E)));
+    } else {
+        e.l("constexpr int LPR = 64 / G;");
     }
-    e.l("const long row = g0 + lane;");
+    e.l("const int gi = lane / LPR;");
+    e.l("const long row = g0 + gi;");
     for (int i = 0; i < ngv; ++i) {
         const int c = gemv_calls[i];
         if (CWV > 1) {
-            e.l(F("float sum%d = 0.f;", c));
-            e.l("if (lane < G) {");
-            e.l(F("  kf_cs t = kf_cs_init(kf_part[%d][team][lane][0]);", i));
-            e.l(F("  for (long si = 1; si < S; ++si) t = kf_cs_add(t, kf_part[%d][team][lane][si]);", i));
-            e.l(F("  sum%d = kf_cs_value(t);", c));
-            e.l("}");
+            e.l(F("kf_cs ac%d = kf_cs_init(0.f);", c));
+            e.l("if (gi < G)");
+            e.l(F("  for (long si = lane %% P; si < S; si += P) ac%d = kf_cs_add(ac%d, kf_part[%d][team][gi][si]);", c, c, i));
+            e.l(F("const float sum%d = kf_cs_value(kf_butterfly_cs<P / 2, 1>(ac%d));", c, c));
         } else {
-            e.l(F("float sum%d = kf_cs_value(ac%d[0]);", c, c));
-            e.l("#pragma unroll");
-            e.l(F("for (int gi = 1; gi < G; ++gi) sum%d = lane == gi ? kf_cs_value(ac%d[gi]) : sum%d;", c, c, c));
+            e.l(F("const float sum%d = kf_cs_value(kf_butterfly_cs<LPR / 2, LPR / U>(ac%d));", c, c));
         }
     }
-    e.l("if (lane < G && row < M) {");
+    e.l("if (gi < G && lane % LPR == 0 && row < M) {");
     e.ind++;
     for (int c : gemv_calls) {
         const Call& k = s.calls[c];
@@ -1001,26 +1003,27 @@ static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls,
     kc.lds_bytes = 16 + (CWV > 1 ? gemv_calls.size() * (size_t)T * G * S * 4 : 0);
     kc.params_json = F("{\"schedule\": \"row-stream\", \"k\": %d, \"waves\": %d, \"group\": %d, \"rows\": %d, \"unroll\": %d, "
                        "\"column_waves\": %d, \"unit_elems\": %d, \"strips\": %ld}",
-                       KU, W, G, T * G, U, CWV, E, S);
+                       1, W, G, T * G, U, CWV, E, S);
     kernel_bytes(s, calls, part, &kc.bytes_read, &kc.bytes_written);
     return kc;
 }
 
 // Sharing a row between waves pays on long rows (fewer rows open at once: GESUMMV
-// n = 16384 302 us with four waves a row, 355 with one) as long as its steps
-// are full; short matrices share rows to have waves at all (512 x 16384: 12 us
+// n = 16384 297 us with four waves a row, 355 with one) as long as its steps
+// are full; short matrices share rows to have waves at all (512 x 16384: 13 us
 // with four waves a row, 40 with one). Elsewhere a wave per row is best: n = 5003
-// 31 us (the strip kernel and its finishing launch 47), n = 10007 117 us. 16-byte
+// 32 us (the strip kernel and its finishing launch 47), n = 10007 120 us; rows of at
+// most 256 columns go four to a wave (200000 x 60 23 us, 41 one by one). 16-byte
 // units of BF16 and FP8 read two to four times their own bytes of x, which two
 // or four rows share (gemv of FP8 16384 x 16384: 52 us with four rows, 66 with
 // two).
-static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E, int K) {
+static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E) {
     StreamGeom g{4, 1, 1, 1};
-    const int64_t ch = (cols + 64 * E * K - 1) / (64 * E * K);   // strips of a row
+    const int64_t ch = (cols + 64 * E - 1) / (64 * E);   // strips of a row
     int64_t pch = 1;
     while (pch < ch) pch *= 2;
-    const int full = std::max(1, 8 / K);   // strips in flight per wave: eight float4 per row and lane
-    if (ch <= 4096 && (rows < 1024 || cols >= 8192)) {
+    const int full = 8;   // strips in flight per wave: eight float4 per row and lane
+    if (ch <= 8192 && (rows < 1024 || cols >= 8192)) {
         g.CWV = (int)std::min<int64_t>(4, pch);
         while (rows >= 1024 && g.CWV > 1) {
             const int64_t step = (int64_t)full * g.CWV;
@@ -1029,12 +1032,12 @@ static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E, int K) {
         }
     }
     if (E > 4) {
-        g.U = K > 1 || ch == 1 ? 1 : 2;
+        g.U = ch == 1 ? 1 : 2;
         g.G = rows >= 1024 ? (ch >= 16 ? 4 : 2) : 1;
         return g;
     }
     g.U = (int)std::min<int64_t>(full, std::max<int64_t>(1, pch / g.CWV));
-    if (g.U * K == 1 && g.CWV == 1 && rows >= 4096) g.G = 4;   // rows of at most 256 columns
+    if (g.U == 1 && g.CWV == 1 && rows >= 4096) g.G = 4;   // rows of at most 256 columns
     return g;
 }
 

@@ -342,19 +342,40 @@ __device__ __forceinline__ kf_cs4 kf_cs4_down(kf_cs4 a, int m) {
     return r;
 }
 
-// Butterfly within aligned groups of NL lanes (NL a power of two, at most 64)
-// on pairs: every lane of a group ends with the merge of the group's pairs.
-template <int NL>
-__device__ __forceinline__ kf_cs kf_group_sum_cs(kf_cs v) {
-    if constexpr (NL == 1) {
+// Butterfly over lane bits MASK, MASK / 2, ..., LOW on pairs (nothing if MASK < LOW).
+template <int MASK, int LOW>
+__device__ __forceinline__ kf_cs kf_butterfly_cs(kf_cs v) {
+    if constexpr (MASK < LOW || MASK == 0) {
         return v;
-    } else if constexpr (NL >= 32) {
-        const kf_f2 s = kf_swap<NL / 2>(v.s, v.s), c = kf_swap<NL / 2>(v.c, v.c);
-        return kf_group_sum_cs<NL / 2>(kf_cs_merge(kf_cs{s.x, c.x}, kf_cs{s.y, c.y}));
+    } else if constexpr (MASK >= 16) {
+        const kf_f2 s = kf_swap<MASK>(v.s, v.s), c = kf_swap<MASK>(v.c, v.c);
+        return kf_butterfly_cs<MASK / 2, LOW>(kf_cs_merge(kf_cs{s.x, c.x}, kf_cs{s.y, c.y}));
     } else {
-        const kf_cs o = {kf_row_xor<NL / 2>(v.s), kf_row_xor<NL / 2>(v.c)};
-        return kf_group_sum_cs<NL / 2>(kf_cs_merge(v, o));
+        const kf_cs o = {kf_row_xor<MASK>(v.s), kf_row_xor<MASK>(v.c)};
+        return kf_butterfly_cs<MASK / 2, LOW>(kf_cs_merge(v, o));
     }
+}
+// Within aligned groups of NL lanes (NL a power of two, at most 64): every lane of a
+// group ends with the merge of the group's pairs.
+template <int NL>
+__device__ __forceinline__ kf_cs kf_group_sum_cs(kf_cs v) { return kf_butterfly_cs<NL / 2, 1>(v); }
+// Partial sums of a row in their order: chain i adds partials i, i + P, ..., and the
+// chains are merged as a butterfly of P lanes would merge them (i with i + P / 2 first).
+template <int P, typename Get>
+__device__ __forceinline__ kf_cs kf_sum_parts(long n, Get get) {
+    kf_cs a[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) a[i] = kf_cs_init(i < n ? get(i) : 0.f);
+    for (long b = P; b < n; b += P) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) a[i] = kf_cs_add(a[i], b + i < n ? get(b + i) : 0.f);
+    }
+#pragma unroll
+    for (int d = P / 2; d >= 1; d /= 2) {
+#pragma unroll
+        for (int i = 0; i < d; ++i) a[i] = kf_cs_merge(a[i], a[i + d]);
+    }
+    return a[0];
 }
 // The same over the whole wave.
 __device__ __forceinline__ kf_cs kf_wave_sum_cs(kf_cs v) { return kf_group_sum_cs<64>(v); }

@@ -82,13 +82,14 @@ std::vector<std::vector<int>> kernels_in_order(const Script& s, const std::vecto
 // for strip kernels in the library's geometry: how a wave adds its rows of a column
 // (row by row in FP32; the sum of each step's rows in FP32; that sum into a (sum,
 // error) pair), turns, the row blocks that a workgroup takes one after another, and
-// then blocks, their number (0: as `rows` gives it)
+// then blocks, their number (0: as `rows` gives it), sub, the parts of a strip whose
+// row sums are kept apart
 enum class ColSum { Plain, Steps, Pairs };
 struct MatParams {
     int k = 0, waves = 0, group = 0, rows = 0, sched = 0, unit = 0;
     bool dyn = false;
     ColSum sums = ColSum::Plain;
-    int turns = 1;
+    int turns = 1, sub = 1;
     int64_t blocks = 0;
 };
 struct VecParams { int unroll = 0, threads = 0, grid = 0; };

@@ -390,6 +390,7 @@ static MatParams library_mat_params(int64_t rows, int64_t cols, int E, bool stor
         r = block_rows(p.blocks);
     }
     p.rows = (int)r;
+    p.sub = p.k;
     return p;
 }
 
@@ -435,6 +436,7 @@ MatParams kernel_mat_params(const Script& s, const std::vector<int>& calls, cons
     if (q.k == p.k && q.waves == p.waves && q.group == p.group && q.rows == p.rows) {
         q.sums = p.sums;
         q.turns = p.turns;
+        q.sub = p.sub;
         q.blocks = p.blocks;
     }
     return q;
