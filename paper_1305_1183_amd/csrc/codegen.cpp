@@ -1278,8 +1278,9 @@ bool needs_rowres(const Script& s, const std::vector<int>& calls) {
 // rows of their own, with no barrier until their column sums are merged at the
 // end. One workgroup per CU as in the wide geometry, so no more partials; short
 // matrices keep four rows per team. Single-pass ATAX, whole plans: 30011 x 1021
-// 77 us -> 27 us (sixteen teams 28), 20000 x 1500 60 -> 27, 32768 x 256 31 -> 13
-// (four rows per group; one row per group 24), 1024 x 1024 9.3 -> 6.4.
+// 82 us -> 25 us, 20000 x 1500 40 -> 25, 32768 x 256 30 -> 11 (four rows per group; one
+// row per group 24), 1024 x 1024 12.3 -> 9.3. Of these 0 to 4% are the pairs in which the
+// 256-column parts of a row dot meet, as they do where waves share a row.
 static RowresGeom rowres_team_geometry(int64_t rows, int64_t cols) {
     RowresGeom g;
     g.W = g.WP = 1;
@@ -1418,6 +1419,11 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
     const int W = geo.W, WP = geo.WP, KP = geo.KP, G = geo.G, T = geo.T;
     int LG = 0;
     while ((1 << LG) < G) ++LG;
+    // row dots of a team end every 256 columns and meet as pairs, like those of waves that
+    // share a row: KPP of them (KP rounded up to a power of two)
+    int KPP = 1, LGK = 0;
+    while (KPP < KP) KPP *= 2;
+    while ((1 << LGK) < G * KPP) ++LGK;
     const int NT = 64 * W * T;
     const long CW = 256L * KP;
     const long R = geo.R;
@@ -1520,7 +1526,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         }
         e.ind--;
         e.l("}");
-        for (int c : gemv_calls) e.l(F("float rp%d[G];", c));
+        for (int c : gemv_calls) e.l(F(T > 1 ? "float rp%d[G * %d];" : "float rp%d[G];", c, KPP));
         for (int c : calls)
             if (s.calls[c].op == Op::Ger) e.l(F("kf_f4 m%d[G][KP];", s.calls[c].out));
         // maps and row dots
@@ -1538,6 +1544,9 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
                     else if (!edge) e.l(F("for (int j = 0; j < KP; ++j) kf_st4_nt(O%d + row * LD%d + (long)(cb + 256u * j), m%d[gi][j]);", k.out, k.out, k.out));
                     else e.l(F("if (row < r1) for (int j = 0; j < KP; ++j) kf_stm_edge(O%d + row * LD%d, (long)(cb + 256u * j), N, m%d[gi][j]);", k.out, k.out, k.out));
                 }
+            } else if (k.op == Op::Gemv && T > 1) {
+                e.l(F("for (int j = 0; j < %d; ++j) rp%d[gi * %d + j] = 0.f;", KPP, c, KPP));
+                e.l(F("for (int j = 0; j < KP; ++j) rp%d[gi * %d + j] = kf_dot4(%s[j], %s, 0.f);", c, KPP, Min.c_str(), cvx(k.in[1]).c_str()));
             } else if (k.op == Op::Gemv) {
                 e.l(F("float t%d = 0.f;", c));
                 e.l(F("for (int j = 0; j < KP; ++j) t%d = kf_dot4(%s[j], %s, t%d);", c, Min.c_str(), cvx(k.in[1]).c_str(), c));
@@ -1549,7 +1558,8 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         // finish the row dots inside the workgroup
         for (int i = 0; i < ngv; ++i) {
             int c = gemv_calls[i];
-            if (T > 1) e.l(F("const float fl%d = kf_rows_reduce<LG>(rp%d);", c, c));   // whole rows: lane gi << (6 - LG) holds row gi
+            // whole rows: lane gi << (6 - LG) holds row gi
+            if (T > 1) e.l(F("const float fl%d = kf_cs_value(kf_butterfly_cs<(32 >> LG), (64 >> %d)>(kf_cs_init(kf_rows_reduce<%d>(rp%d))));", c, LGK, LGK, c));
             else e.l(F("{ const float sw = kf_rows_reduce<LG>(rp%d); if ((lane & ((64 >> LG) - 1)) == 0) kf_part[slot][%d][lane >> (6 - LG)][wave] = sw; }", c, i));
         }
         if (ngv && T == 1) e.l("__syncthreads();");
