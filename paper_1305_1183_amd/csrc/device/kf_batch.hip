@@ -653,8 +653,9 @@ __device__ __forceinline__ void kfb_w_gemv(const kfb_inst& I, __amdgpu_buffer_rs
 
 // K1: WC waves share a row (4 above n = 512: lane t of the workgroup owns chunks
 // t + 256 k of every row and its column sums need no exchange; 1 below: four row
-// groups whose column sums meet in LDS). A step's G rows are summed first, which
-// keeps the FP32 chains short.
+// groups whose column sums meet in LDS). A step's G rows are summed first, and where
+// one lane has all rows of a block the steps' sums meet as pairs, as those of four
+// row groups did: no longer FP32 chains than theirs.
 template <int WC, int K, int LG, bool SPLIT>
 __device__ void kfb_w_gemver_k1(const kfb_inst& I, int blk, float* __restrict__ arena, float* __restrict__ ws,
                                 unsigned* sync, Shared& sh) {
@@ -669,6 +670,7 @@ __device__ void kfb_w_gemver_k1(const kfb_inst& I, int blk, float* __restrict__ 
     const float* __restrict__ z = arena + I.v[5];
     float* __restrict__ x = arena + I.v[6];
     kf_f4 v1[K], v2[K], acc[K];
+    kf_cs4 tot[K];   // WC 4: a lane has all rows of the block, its steps' sums meet as pairs
     kfb_cols cs[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
@@ -677,6 +679,7 @@ __device__ void kfb_w_gemver_k1(const kfb_inst& I, int blk, float* __restrict__ 
         v1[k] = kfb_ldv(arena + I.v[1], col, n);
         v2[k] = kfb_ldv(arena + I.v[3], col, n);
         acc[k] = kf_zero4();
+        tot[k] = kf_cs4_init(kf_zero4());
     }
     kf_f4 an[G][K];
     float u1n, u2n, yn;
@@ -718,13 +721,16 @@ __device__ void kfb_w_gemver_k1(const kfb_inst& I, int blk, float* __restrict__ 
             }
         }
 #pragma unroll
-        for (int k = 0; k < K; ++k) acc[k] += s[k];
+        for (int k = 0; k < K; ++k) {
+            if constexpr (WC == 4) tot[k] = kf_cs4_add(tot[k], s[k]);
+            else acc[k] += s[k];
+        }
     }
     // column sums of the block at chunk c, each chunk from one thread
     auto columns = [&](auto emit) {
         if constexpr (WC == 4) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) emit(t + 256 * k, acc[k]);
+            for (int k = 0; k < K; ++k) emit(t + 256 * k, kf_cs4_value(tot[k]));
         } else {
             kfb_colsum<6, K>(acc, sh.red, emit);
         }
