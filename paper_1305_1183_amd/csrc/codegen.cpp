@@ -1319,6 +1319,7 @@ RowresGeom rowres_geometry(int64_t rows, int64_t cols, const MatParams& p) {
 // lane; the margin is for addresses, row partials and temporaries.
 static constexpr int kRowresBudgetHeld = 64;   // a gemv and a gemtv: rows held through the group's barrier
 static constexpr int kRowresBudget = 96;       // the others
+static constexpr int kRowresTeamBudget = 160;  // teams of one wave, eight to a workgroup: 256 VGPRs per lane
 static int rowres_pressure(int KP, int G, size_t nmat, size_t ncv_reg, size_t nacc) {
     return 4 * KP * (G * (int)nmat + (int)ncv_reg + (int)nacc);
 }
@@ -1410,7 +1411,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         RowresGeom tg = rowres_team_geometry(M, N);
         tg.R = std::max(tg.R, (rowres_geometry(M, N, p0).R + tg.G - 1) / tg.G * tg.G);   // never more partials than the wide geometry
         const size_t lds = 16 + rowv.size() * (size_t)tg.R * 4 + gemtv_calls.size() * (size_t)tg.T * tg.KP * 1024;
-        if (lds <= 160 * 1024 && rowres_pressure(tg.KP, tg.G, nheld, colv.size(), gemtv_calls.size()) <= 160) {
+        if (lds <= 160 * 1024 && rowres_pressure(tg.KP, tg.G, nheld, colv.size(), gemtv_calls.size()) <= kRowresTeamBudget) {
             geo = tg;
             colv_lds.clear();
             colv_glob.clear();
@@ -1742,7 +1743,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
     // vectors loaded from global memory count too: the loads of a group are
     // all in flight together
     kc.reg_estimate = rowres_pressure(KP, G, nheld, ncv_reg() + colv_glob.size(), gemtv_calls.size());
-    kc.over_budget = kc.reg_estimate > budget;
+    kc.over_budget = kc.reg_estimate > (T > 1 ? kRowresTeamBudget : budget);
     kc.params_json = F("{\"schedule\": \"row-resident\", \"waves\": %d, \"teams\": %d, \"group\": %d, \"rows\": %ld, \"kp\": %d, \"row_blocks\": %ld, "
                        "\"register_estimate\": %d, \"over_register_budget\": %s}",
                        W, T, G, R, KP, NB, kc.reg_estimate, kc.over_budget ? "true" : "false");
