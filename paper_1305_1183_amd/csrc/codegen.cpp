@@ -186,6 +186,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
                           const std::vector<int>& part, const MatParams& p) {
     KernelCode kc;
     kc.mat = true;
+    kc.geom = p;
     kc.calls = calls;
     const int kid = part[calls[0]];
     const Space sp = call_space(s, calls[0]);
@@ -777,6 +778,10 @@ static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls,
     StreamGeom geo = stream_geometry(M, N, E);
     if (gemv_calls.size() * (size_t)(geo.W / geo.CWV) * geo.G * ((N + 64L * E - 1) / (64L * E)) * 4 > 32 * 1024) geo.CWV = 1;
     const int W = geo.W, G = geo.G, U = geo.U, CWV = geo.CWV, T = W / CWV, NT = 64 * W;
+    kc.geom.k = 1;
+    kc.geom.waves = W;
+    kc.geom.group = G;
+    kc.geom.rows = T * G;
     const long S = (N + 64L * E - 1) / (64L * E);
     int LGU = 0;
     while ((1 << LGU) < G * U) ++LGU;
@@ -2052,7 +2057,9 @@ void kernel_features(const Script& s, const KernelCode& kc, const std::vector<in
     f[14] = (float)vi;
     f[15] = (float)vo;
     if (sp.mat) {
-        MatParams p = default_mat_params(sp.a, sp.b, mp);   // the point as the model knows it
+        // the point, and the geometry that the library took where none was asked for
+        const bool library = library_geometry(mp) && !needs_rowres(s, kc.calls);
+        const MatParams p = library ? kc.geom : default_mat_params(sp.a, sp.b, mp);
         f[16] = (float)p.k;
         f[17] = (float)p.waves;
         f[18] = lg2(p.group);

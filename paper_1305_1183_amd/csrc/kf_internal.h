@@ -149,6 +149,7 @@ struct KernelCode {
     std::vector<int> calls;
     bool mat = false;
     bool stream = false;           // rows streamed by whole waves (no gemtv, library geometry)
+    MatParams geom;                // what a strip or row-stream kernel was generated with
     // Row-resident kernels: the generator's estimate of the VGPRs per lane a row
     // group keeps live, and whether it exceeds the register budget (such a
     // kernel likely spills to scratch memory)

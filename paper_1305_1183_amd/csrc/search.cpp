@@ -131,7 +131,16 @@ kf_status predict_kernel_additive(const kf_plan* p, const PlanKernel& pk, const 
     const KernelCode& kc = pk.code;
     const Space sp = call_space(p->s, kc.calls[0]);
     const bool mat = sp.mat;
+    // Strip environment: the point the kernel was generated with, as
+    // kf_plan_kernel_params reports it (row-stream kernels: nothing requested, all zero).
+    // A table without that environment prices a kernel in the library's geometry as
+    // the small workgroups of default_mat_params.
     MatParams mp = mat ? default_mat_params(sp.a, sp.b, pk.mp) : MatParams();
+    if (mat && library_geometry(pk.mp)) {
+        const MatParams own = kc.stream ? MatParams() : kc.geom;
+        for (int i = 0; i < n; ++i)
+            if (env_match(table[i], 1, own, VecParams())) { mp = own; break; }
+    }
     VecParams vp = mat ? VecParams() : default_vec_params(sp.a, pk.vp);
     if (!mat && pk.vp.grid > 0) vp.grid = pk.vp.grid;  // the environment is the requested point (grid is capped for short vectors)
     const bool rowres = mat && (pk.mp.sched == 1 || needs_rowres(p->s, kc.calls));
