@@ -739,7 +739,12 @@ static bool is_stream(const Script& s, const std::vector<int>& calls, const MatP
     }
     // eight float4 of every row and column vector are in flight per lane: more
     // operands than this would spill
-    return gemv && 32 * (mats.size() + cols.size()) <= 192;
+    if (!gemv || 32 * (mats.size() + cols.size()) > 192) return false;
+    // a launch has fewer than 2^32 threads: past that, strips of many rows a workgroup
+    const Space sp = call_space(s, calls[0]);
+    const StreamGeom g = stream_geometry(sp.a, sp.b, kernel_unit_elems(s, calls, p.unit));
+    const int64_t per = (int64_t)(g.W / g.CWV) * g.G;
+    return (sp.a + per - 1) / per * g.W * 64 < ((int64_t)1 << 32);
 }
 
 static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls, const std::vector<int>& part,
