@@ -192,9 +192,16 @@ kf_quantize_rows_kernel(const float* __restrict__ A, long rows, long cols, long 
 template <int FP8, int T, int K>
 hipError_t launch(const float* A, long rows, long cols, long lda, void* codes, long ldq, float* scales, hipStream_t st) {
     constexpr int NT = T > 256 ? T : 256, RPB = NT / T;
-    hipLaunchKernelGGL((kf_quantize_rows_kernel<FP8, T, K>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(NT), 0, st, A,
-                       rows, cols, lda, codes, ldq, scales);
-    return hipGetLastError();
+    // a launch has fewer than 2^32 threads: 4194303 rows of 1024 lanes
+    constexpr long most = ((1L << 32) - 1) / NT * RPB;
+    for (long r = 0; r < rows; r += most) {
+        const long n = rows - r < most ? rows - r : most;
+        hipLaunchKernelGGL((kf_quantize_rows_kernel<FP8, T, K>), dim3((unsigned)((n + RPB - 1) / RPB)), dim3(NT), 0, st,
+                           A + r * lda, n, cols, lda, static_cast<char*>(codes) + r * ldq * (FP8 ? 1 : 2), ldq, scales + r);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // Lanes per row and chunks per lane: the fewest lanes that hold the row in
