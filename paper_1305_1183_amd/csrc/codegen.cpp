@@ -474,7 +474,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
             if (SUB > 1) e.l("const long part = sidx * SUB + (lane >> (6 - LG)) % SUB;");
             else e.l("const long part = sidx;");
             e.l("(void)part;");
-            e.l(F("if ((lane & ((64 >> LG) - 1)) == 0%s%s) {", edge ? " && row < r1" : "", SUB > 1 && (p.dyn || S * SUB != SR) ? " && part < SR" : ""));
+            e.l(F("if ((lane & ((64 >> LG) - 1)) == 0%s%s) {", edge ? " && row < r1" : "", S * SUB != SR && SUB > 1 ? " && part < SR" : ""));
             e.ind++;
             if (!row_part) {
                 row_epilogue("row");
@@ -690,7 +690,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     if (p.dyn) {
         mainl.dyn_grid = 1;
         mainl.dyn_c = C;
-        mainl.dyn_r = R * TB;
+        mainl.dyn_r = R;
     }
     kc.launches.push_back(mainl);
     if (row_part || col_part) {

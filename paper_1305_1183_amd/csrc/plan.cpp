@@ -399,6 +399,10 @@ bool library_geometry(const MatParams& p) { return p.sched == 0 && p.k <= 0 && p
 MatParams kernel_mat_params(const Script& s, const std::vector<int>& calls, const MatParams& req) {
     const Space sp = call_space(s, calls[0]);
     const int E = kernel_unit_elems(s, calls, req.unit);
+    // A plan compiled for shapes up to the declared one keeps the small workgroups: the
+    // blocks that fill the chip at the declared shape are few at a smaller one (BiCGK
+    // declared 16384 x 16384, run at 4096 x 4096 29 us, with its geometry 92; at 16384 176, 174).
+    if (req.dyn) return default_mat_params(sp.a, sp.b, req, E);
     const std::set<int> mine(calls.begin(), calls.end());
     std::set<int> mats, cols, rows;
     int gemtv = 0;
