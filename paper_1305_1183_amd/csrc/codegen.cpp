@@ -364,8 +364,15 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
     };
 
     auto emit_loads = [&](bool edge) {
-        // loads of every matrix read from HBM (load routines)
+        // loads of every matrix read from HBM (load routines). The 16-byte units of a step
+        // are loaded before the first is decoded. From four on the compiler has to be
+        // told: it puts a decode, and the wait for its unit, between them (BiCGK of FP8
+        // 32768 x 32768, two units a lane and two rows a step: 329 us so, 237 in order;
+        // steps of two units 0 to 4% slower in order).
         for (int v : mat_in) e.l(F("kf_f4 L%d[G][K];", v));
+        auto units = [&](int v) { return s.values[v].dtype != KF_F32 && E > 4 ? U * (E * dtype_size(s.values[v].dtype) / 16) : 0; };
+        for (int v : mat_in)
+            if (!edge && units(v)) e.l(F("kf_u4 Q%d[G][%d];", v, units(v)));
         e.l("#pragma unroll");
         e.l("for (int gi = 0; gi < G; ++gi) {");
         e.ind++;
@@ -391,7 +398,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
                 e.ind++;
                 e.l(F("const long cu0 = col[(u / %d) * EG] + (long)(u %% %d) * %d;", E / per, E / per, per));
                 if (!edge) {
-                    e.l(F("%s(kf_ldu_nt(M%d + (row * LD%d + cu0) * %d), &L%d[gi][u * %d]);", dec, v, v, es, v, EQ));
+                    e.l(F("Q%d[gi][u] = kf_ldu_nt(M%d + (row * LD%d + cu0) * %d);", v, v, v, es));
                 } else {
                     e.l(F("if (row < r1 && cu0 < N) { %s(kf_ldu_nt(M%d + (row * LD%d + cu0) * %d), &L%d[gi][u * %d]);", dec, v, v, es, v, EQ));
                     e.l(F("  for (int q = 0; q < %d; ++q) L%d[gi][u * %d + q] = kf_mask4(L%d[gi][u * %d + q], cu0 + 4 * q, N); }", EQ, v, EQ, v, EQ));
@@ -406,6 +413,17 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         }
         e.ind--;
         e.l("}");
+        int in_order = 0;
+        for (int v : mat_in) in_order += edge ? 0 : units(v) * G;
+        if (in_order >= 4) e.l("__builtin_amdgcn_sched_barrier(0x84);");   // scalar and LDS instructions may cross
+        for (int v : mat_in) {
+            if (edge || !units(v)) continue;
+            const bool bf = s.values[v].dtype == KF_BF16;
+            e.l("#pragma unroll");
+            e.l("for (int gi = 0; gi < G; ++gi)");
+            e.l("#pragma unroll");
+            e.l(F("for (int u = 0; u < %d; ++u) %s(Q%d[gi][u], &L%d[gi][u * %d]);", units(v), bf ? "kf_dec_bf16" : "kf_dec_fp8", v, v, bf ? 2 : 4));
+        }
     };
     auto emit_compute = [&](bool edge) {
         for (int c : gemv_calls) e.l(F("float rp%d[G * SUB];", c));
