@@ -11,9 +11,9 @@
 #include "kf_batch_defs.h"
 #include "kf_internal.h"
 
-hipError_t kfb_launch(const kfb_inst* insts, const kfb_item* items, int nitems, int item0, int grid, int persistent,
-                      float* arena, float* ws, unsigned* sync, unsigned spin_limit, hipStream_t st);
-hipError_t kfb_resident_blocks(int* per_cu, int* cus);
+hipError_t kfb_launch(bool menu, const kfb_inst* insts, const kfb_item* items, int nitems, int item0, int grid,
+                      int persistent, float* arena, float* ws, unsigned* sync, unsigned spin_limit, hipStream_t st);
+hipError_t kfb_resident_blocks(bool menu, int* per_cu, int* cus);
 
 using kf::set_error;
 
@@ -47,6 +47,7 @@ struct kf_batch {
     int64_t bytes_read = 0, bytes_written = 0;
     int32_t rows[2][KFB_BUCKETS];
     int32_t tile[2][KFB_BUCKETS];   // entry of the tile menu per kind and bucket
+    bool menu = false;              // some instance takes a tile that is not the default
     int32_t grid_req = 0;
     uint32_t spin_limit = 1u << 22;
     // bound state
@@ -143,6 +144,7 @@ kf_status kf_batch_create(int64_t count, const int32_t* kind, const int64_t* n, 
             I.ld = (int32_t)((n[i] + 31) / 32 * 32);
             I.bucket = kfb_bucket(I.n);
             I.tile = b->tile[I.kind][I.bucket];
+            b->menu = b->menu || I.tile != 0;
             I.rows = b->rows[I.kind][I.bucket];
             I.nblk = (I.n + I.rows - 1) / I.rows;
             if (I.nblk == 1) I.rows = I.n;
@@ -377,7 +379,7 @@ kf_status kf_batch_bind(kf_batch* b, float* arena, void* workspace, void* stream
         b->grid = b->grid_req;
     } else {
         int per_cu = 0, cus = 0;
-        if (kfb_resident_blocks(&per_cu, &cus) != hipSuccess || per_cu < 1 || cus < 1)
+        if (kfb_resident_blocks(b->menu, &per_cu, &cus) != hipSuccess || per_cu < 1 || cus < 1)
             return set_error(KF_ERR_HIP, "occupancy query failed");
         b->grid = per_cu * cus;
     }
@@ -389,15 +391,15 @@ static kf_status batch_launch(kf_batch* b, int which, hipStream_t st) {
     if (b->insts.empty()) return KF_OK;
     const int nq = (int)b->queue.size();
     if (which == 0) {
-        if (kfb_launch(b->insts_ptr(), b->queue_ptr(), nq, 0, b->grid, 1, b->arena, b->part_ptr(), b->sync_ptr(),
+        if (kfb_launch(b->menu, b->insts_ptr(), b->queue_ptr(), nq, 0, b->grid, 1, b->arena, b->part_ptr(), b->sync_ptr(),
                        b->spin_limit, st) != hipSuccess)
             return set_error(KF_ERR_HIP, "persistent launch failed");
         return KF_OK;
     }
     for (size_t i = 0; i < b->insts.size(); ++i) {
-        if (kfb_launch(b->insts_ptr(), b->by_inst_ptr(), nq, b->first1[i], b->count1[i], 0, b->arena, b->part_ptr(),
+        if (kfb_launch(b->menu, b->insts_ptr(), b->by_inst_ptr(), nq, b->first1[i], b->count1[i], 0, b->arena, b->part_ptr(),
                        b->sync_ptr(), b->spin_limit, st) != hipSuccess ||
-            kfb_launch(b->insts_ptr(), b->by_inst_ptr(), nq, b->first2[i], b->count2[i], 0, b->arena, b->part_ptr(),
+            kfb_launch(b->menu, b->insts_ptr(), b->by_inst_ptr(), nq, b->first2[i], b->count2[i], 0, b->arena, b->part_ptr(),
                        b->sync_ptr(), b->spin_limit, st) != hipSuccess)
             return set_error(KF_ERR_HIP, "instance launch failed");
     }

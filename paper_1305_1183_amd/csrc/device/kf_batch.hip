@@ -817,31 +817,36 @@ __device__ __forceinline__ void kfb_tile_run(const kfb_inst& I, int phase, int b
     }
 }
 
-template <int KIND, int B>
+template <int KIND, int B, bool MENU>
 __device__ __forceinline__ void kfb_bucket_run(const kfb_inst& I, int phase, int blk, float* arena, float* ws,
                                                unsigned* sync, unsigned spin_limit, Shared& sh) {
-    switch (I.tile) {
-    case 1: kfb_tile_run<KIND, B, 1>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
-    case 2: kfb_tile_run<KIND, B, 2>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
-    default: kfb_tile_run<KIND, B, 0>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
+    if constexpr (MENU) {
+        if (I.tile == 1) { kfb_tile_run<KIND, B, 1>(I, phase, blk, arena, ws, sync, spin_limit, sh); return; }
+        if (I.tile == 2) { kfb_tile_run<KIND, B, 2>(I, phase, blk, arena, ws, sync, spin_limit, sh); return; }
     }
+    kfb_tile_run<KIND, B, 0>(I, phase, blk, arena, ws, sync, spin_limit, sh);
 }
 
-template <int KIND>
+template <int KIND, bool MENU>
 __device__ __forceinline__ void kfb_kind_run(const kfb_inst& I, int phase, int blk, float* arena, float* ws,
                                              unsigned* sync, unsigned spin_limit, Shared& sh) {
     switch (I.bucket) {
-    case 0: kfb_bucket_run<KIND, 0>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
-    case 1: kfb_bucket_run<KIND, 1>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
-    case 2: kfb_bucket_run<KIND, 2>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
-    case 3: kfb_bucket_run<KIND, 3>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
-    case 4: kfb_bucket_run<KIND, 4>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
-    default: kfb_bucket_run<KIND, 5>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
+    case 0: kfb_bucket_run<KIND, 0, MENU>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
+    case 1: kfb_bucket_run<KIND, 1, MENU>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
+    case 2: kfb_bucket_run<KIND, 2, MENU>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
+    case 3: kfb_bucket_run<KIND, 3, MENU>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
+    case 4: kfb_bucket_run<KIND, 4, MENU>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
+    default: kfb_bucket_run<KIND, 5, MENU>(I, phase, blk, arena, ws, sync, spin_limit, sh); break;
     }
 }
 
 // Three waves per SIMD (168 VGPRs): GEMVER's steps of eight 16-byte loads per lane
 // keep the next step's loads beside them.
+// MENU: with every tile of the menu, for batches that ask for one that is not the
+// default. Without them the code is a third of the size; its first pass through each
+// CU's instruction cache is what a few small instances wait for (64 GEMVER of n = 128:
+// 27.9 us without the menu, 32.2 with it; 512 of them 39.6 and 43.8).
+template <bool MENU>
 __global__ void __launch_bounds__(KFB_THREADS) __attribute__((amdgpu_waves_per_eu(3, 8)))
 kfb_kernel(const kfb_inst* __restrict__ insts, const kfb_item* __restrict__ items, int nitems, int item0,
            int persistent, float* arena, float* ws, unsigned* sync, unsigned spin_limit) {
@@ -862,8 +867,8 @@ kfb_kernel(const kfb_inst* __restrict__ insts, const kfb_item* __restrict__ item
         const int phase = item.phase_blk >> 24;
         const int blk = item.phase_blk & 0xffffff;
         // the instance's tile from the menu of its kind and size bucket
-        if (I.kind == 0) kfb_kind_run<0>(I, phase, blk, arena, ws, sync, spin_limit, sh);   // BiCGK
-        else kfb_kind_run<1>(I, phase, blk, arena, ws, sync, spin_limit, sh);
+        if (I.kind == 0) kfb_kind_run<0, MENU>(I, phase, blk, arena, ws, sync, spin_limit, sh);   // BiCGK
+        else kfb_kind_run<1, MENU>(I, phase, blk, arena, ws, sync, spin_limit, sh);
         if (!persistent) break;
         __syncthreads();
     }
@@ -879,16 +884,16 @@ kfb_kernel(const kfb_inst* __restrict__ insts, const kfb_item* __restrict__ item
 
 // Persistent launch (grid workgroups draining the queue) or a direct launch of
 // items item0 .. item0 + grid - 1, one per workgroup.
-hipError_t kfb_launch(const kfb_inst* insts, const kfb_item* items, int nitems, int item0, int grid, int persistent,
-                      float* arena, float* ws, unsigned* sync, unsigned spin_limit, hipStream_t st) {
+hipError_t kfb_launch(bool menu, const kfb_inst* insts, const kfb_item* items, int nitems, int item0, int grid,
+                      int persistent, float* arena, float* ws, unsigned* sync, unsigned spin_limit, hipStream_t st) {
     if (grid <= 0) return hipSuccess;
-    hipLaunchKernelGGL(kfb_kernel, dim3(grid), dim3(KFB_THREADS), 0, st, insts, items, nitems, item0, persistent,
+    hipLaunchKernelGGL(menu ? kfb_kernel<true> : kfb_kernel<false>, dim3(grid), dim3(KFB_THREADS), 0, st, insts, items, nitems, item0, persistent,
                        arena, ws, sync, spin_limit);
     return hipGetLastError();
 }
 
-hipError_t kfb_resident_blocks(int* per_cu, int* cus) {
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, kfb_kernel, KFB_THREADS, 0);
+hipError_t kfb_resident_blocks(bool menu, int* per_cu, int* cus) {
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, menu ? kfb_kernel<true> : kfb_kernel<false>, KFB_THREADS, 0);
     if (e != hipSuccess) return e;
     int dev = 0;
     e = hipGetDevice(&dev);
