@@ -18,7 +18,7 @@
 namespace kf {
 hipError_t mlp_gemm(int M, int N, int K, const float* A, long sai, long sak, const float* B, long sbk, long sbj,
                     float* C, long ldc, const float* bias, int relu, const float* mask, long ldm, hipStream_t st);
-bool mlp_rows_fit(int d, int h);
+bool mlp_rows_pay(int d, int h, int L, long n, bool grad);
 hipError_t mlp_rows(int n, int d, int h, int L, const float* P, const float* X, const float* y, float* H, float* dZ,
                     float* pred, float* dpred, hipStream_t st);
 hipError_t mlp_wgrad(int n, int count, const float* const* A, const float* const* D, float* const* G, const int* in,
@@ -39,12 +39,12 @@ struct kf_mlp {
 namespace {
 
 // Workspace: L activation buffers and L pre-activation gradients (n x h each),
-// the prediction and its gradient (n each), padded. Networks too wide for the
-// block kernel, and callers with a smaller workspace, run layer by layer with
+// the prediction and its gradient (n each), padded. Networks for which the block
+// kernel does not pay, and callers with a smaller workspace, run layer by layer with
 // two gradient buffers in turn, which needs ws_floats_min.
 size_t ws_floats_min(const kf_mlp* m, long n) { return (size_t)(m->L + 2) * n * m->h + 2 * (size_t)n + 64; }
 size_t ws_floats(const kf_mlp* m, long n) {
-    if (!mlp_rows_fit(m->d, m->h)) return ws_floats_min(m, n);
+    if (!mlp_rows_pay(m->d, m->h, m->L, n, true)) return ws_floats_min(m, n);
     return (size_t)std::max(m->L + 2, 2 * m->L) * n * m->h + 2 * (size_t)n + 64;
 }
 
@@ -144,7 +144,7 @@ kf_status kf_mlp_forward(const kf_mlp* m, const float* params, const float* X, i
     if (ws_bytes < ws_floats_min(m, n) * sizeof(float)) return set_error(KF_ERR_WORKSPACE, "MLP workspace too small");
     hipStream_t st = (hipStream_t)stream;
     float* w = (float*)ws;
-    if (mlp_rows_fit(m->d, m->h)) {
+    if (mlp_rows_pay(m->d, m->h, m->L, n, false)) {
         HIPCHK(mlp_rows(n, m->d, m->h, m->L, params, X, nullptr, nullptr, nullptr, pred, nullptr, st));
         return KF_OK;
     }
@@ -165,7 +165,7 @@ kf_status kf_mlp_loss_grad(const kf_mlp* m, const float* params, const float* X,
     auto H = [&](int l) -> const float* { return l == 0 ? X : w + (size_t)(l - 1) * n * h; };  // input of layer l
     // the block kernel keeps every layer's gradient, so that all weight gradients
     // come from one launch: 3 launches a step against 5 L + 5
-    if (mlp_rows_fit(m->d, h) && ws_bytes >= ws_floats(m, n) * sizeof(float)) {
+    if (mlp_rows_pay(m->d, h, L, n, true) && ws_bytes >= ws_floats(m, n) * sizeof(float)) {
         float* dZ = w + (size_t)L * n * h;
         float* pred = w + (size_t)2 * L * n * h;
         float* dpred = pred + n;

@@ -583,9 +583,23 @@ hipError_t mlp_gemm(int M, int N, int K, const float* A, long sai, long sak, con
     return hipGetLastError();
 }
 
-// Widths whose two 16-row tiles fit 64 KiB of LDS; wider networks are no longer
-// bound by launches and go layer by layer.
-bool mlp_rows_fit(int d, int h) { return d <= 480 && h <= 480; }
+// Whether a network takes the block kernel: the widths whose two 16-row tiles fit 64
+// KiB of LDS, where it is the faster route. A workgroup walks all layers of its 16
+// samples, so few samples leave a wide network to few workgroups, whose every layer is
+// bound by the latency of its weights; one launch a layer spreads the layer over the
+// chip. us of a gradient (of predictions), block against layer by layer, at d = 32:
+//  - three layers of 128: n = 16 16 (6.5) against 62 (26), n = 32768 0.25 (0.3) times;
+//  - three layers of 480: n = 16 509 (249) against 167 (105), n = 1024 2.2 (1.6) times,
+//    n = 4096 0.9 (0.7) times; eight layers n = 4096 0.94 (1.4) times, n = 32768 0.8 both;
+//  - three layers of 16, n = 32768: predictions 1.6 times, gradients 0.3 times; and
+//    predictions of 480 inputs 1.06 times already at n = 16.
+bool mlp_rows_pay(int d, int h, int L, long n, bool grad) {
+    if (d > 480 || h > 480) return false;
+    if (grad) return h <= 128 || n >= 4096;
+    if (h > 128) return n >= (L <= 4 ? 4096 : 16384);
+    const bool tiled = d % 32 == 0 && (h == 32 || h == 64 || h == 128);
+    return n <= 4096 ? d <= 128 || h >= 32 : h >= 64 || (tiled && d <= 128);
+}
 
 hipError_t mlp_rows(int n, int d, int h, int L, const float* P, const float* X, const float* y, float* H, float* dZ,
                     float* pred, float* dpred, hipStream_t st) {
