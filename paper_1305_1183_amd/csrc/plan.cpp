@@ -327,7 +327,11 @@ MatParams default_mat_params(int64_t rows, int64_t cols, const MatParams& req, i
 //    from eight waves a CU: GEMVER's first kernel n = 16384 346 (sixteen waves of
 //    the next line 413, 2048 small workgroups 361). Rows that do not start on
 //    1 KiB boundaries take two float4 per lane, as strip edges then cost part of a
-//    line on each side: n = 9000 131 (one float4: 163).
+//    line on each side: n = 9000 131 (one float4: 163). Rows of fewer than 256 columns
+//    fill part of a strip and want sixteen waves a CU: 89702 x 100 32 (eight: 44); so do
+//    BF16 and FP8 sources, which read less than they store: BF16 n = 4000 28 (32).
+//    Without column sums there are no partials to save, and narrow matrices keep the
+//    small workgroups: ger 89702 x 100 23 (40), 20000 x 700 29 (31), 9000 163 (128).
 //  - other FP32 kernels: one workgroup of sixteen waves per CU, 2 KiB strips. BiCGK
 //    n = 16384 165 (2048 workgroups of four waves: 186), 5003 21.3 (26.5), 12001 94
 //    (124), 700 x 16000 12.5 (22.6).
@@ -352,13 +356,15 @@ MatParams default_mat_params(int64_t rows, int64_t cols, const MatParams& req, i
 //    us, 688 with pairs every 128 rows; FP8 178 and 258). So do blocks of more than 4096
 //    rows, whose vectors are staged in LDS (GEMVER n = 24000 1230 us; 1500 with 282
 //    workgroups of one block each).
-static MatParams library_mat_params(int64_t rows, int64_t cols, int E, bool stores, bool column_sums) {
+static MatParams library_mat_params(int64_t rows, int64_t cols, int E, bool stores, bool column_sums, bool quantized) {
     MatParams p;
     const int64_t few = default_mat_params(rows, cols, MatParams(), E).rows, chain = few / 4;
     const int64_t by_row = chain + chain / 16, by_step = (11 * chain - 17) / 5;   // rows of a wave, within 5% of its error
     int per_cu;
     const bool small = (double)rows * (double)cols <= 6e6, general = !small && !stores;
     if (small) { p.k = 1; p.waves = 8; p.group = 4; per_cu = 16; }
+    else if (stores && !column_sums && cols < 1024) return default_mat_params(rows, cols, p, E);
+    else if (stores && (cols < 256 || (quantized && cols % 256 != 0))) { p.k = 1; p.waves = 8; p.group = 4; per_cu = 16; }
     else if (stores) { const bool line = cols % 256 == 0; p.k = line ? 1 : 2; p.waves = 8; p.group = line ? 4 : 2; per_cu = 8; }
     else if (E == 4) { p.k = 2; p.waves = 16; p.group = 1; per_cu = 16; }
     else if (cols <= 2 * 64 * E) { p.k = 1; p.waves = 16; p.group = 2; per_cu = 16; }
@@ -424,7 +430,7 @@ MatParams kernel_mat_params(const Script& s, const std::vector<int>& calls, cons
         stores = stores || o.output;
         for (int d : o.consumers) stores = stores || !mine.count(d);
     }
-    MatParams p = library_mat_params(sp.a, sp.b, E, stores, gemtv > 0);
+    MatParams p = library_mat_params(sp.a, sp.b, E, stores, gemtv > 0, kernel_has_quantized(s, calls));
     // kernels of so many operands that a lane's rows, vectors and accumulators
     // outgrow the registers (128 with sixteen waves in a workgroup, 256 with
     // eight) or the staged vectors and wave sums the LDS keep the small workgroups
