@@ -741,26 +741,43 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
 // waves share a row (strips cw, cw + CWV, ... in steps); the strip sums then meet in LDS
 // and as many lanes per row take them up. Either way the pairs are merged by a butterfly.
 struct StreamGeom { int W, G, U, CWV; };
-static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E);
+static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E, int row_regs, int cols_regs);
+
+// The matrices a row-stream kernel reads and its column vectors.
+static void stream_operands(const Script& s, const std::vector<int>& calls, std::set<int>* mats, std::set<int>* cols) {
+    for (int c : calls) {
+        const Call& k = s.calls[c];
+        if (s.values[k.in[0]].producer < 0 || std::find(calls.begin(), calls.end(), s.values[k.in[0]].producer) == calls.end())
+            mats->insert(k.in[0]);
+        cols->insert(k.op == Op::Gemv ? k.in[1] : k.in[2]);
+    }
+}
+
+static StreamGeom stream_geometry(const Script& s, const std::vector<int>& calls, int E) {
+    std::set<int> mats, cols;
+    stream_operands(s, calls, &mats, &cols);
+    int row = 0;
+    for (int v : mats) row += E * dtype_size(s.values[v].dtype) / 4;
+    const Space sp = call_space(s, calls[0]);
+    return stream_geometry(sp.a, sp.b, E, row, E * (int)cols.size());
+}
 
 static bool is_stream(const Script& s, const std::vector<int>& calls, const MatParams& p) {
     if (!library_geometry(p)) return false;
-    std::set<int> mats, cols;
     bool gemv = false;
     for (int c : calls) {
-        const Call& k = s.calls[c];
-        if (k.op == Op::Gemtv) return false;
-        if (k.op == Op::Gemv) gemv = true;
-        if (s.values[k.in[0]].producer < 0 || std::find(calls.begin(), calls.end(), s.values[k.in[0]].producer) == calls.end())
-            mats.insert(k.in[0]);
-        cols.insert(k.op == Op::Gemv ? k.in[1] : k.in[2]);
+        if (s.calls[c].op == Op::Gemtv) return false;
+        gemv = gemv || s.calls[c].op == Op::Gemv;
     }
-    // eight float4 of every row and column vector are in flight per lane: more
-    // operands than this would spill
-    if (!gemv || 32 * (mats.size() + cols.size()) > 192) return false;
+    // FP32 kernels have eight float4 of every row and column vector in flight per lane: six
+    // operands fill the registers (five matrices and a vector 256 VGPRs, without spills).
+    // Kernels with 16-byte units take fewer rows a wave instead (kStreamBudget).
+    std::set<int> mats, cols;
+    stream_operands(s, calls, &mats, &cols);
+    if (!gemv || mats.size() + cols.size() > 6) return false;
     // a launch has fewer than 2^32 threads: past that, strips of many rows a workgroup
     const Space sp = call_space(s, calls[0]);
-    const StreamGeom g = stream_geometry(sp.a, sp.b, kernel_unit_elems(s, calls, p.unit));
+    const StreamGeom g = stream_geometry(s, calls, kernel_unit_elems(s, calls, p.unit));
     const int64_t per = (int64_t)(g.W / g.CWV) * g.G;
     return (sp.a + per - 1) / per * g.W * 64 < ((int64_t)1 << 32);
 }
@@ -798,7 +815,7 @@ static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls,
         if (s.values[v].scale >= 0) push_u(rowv, s.values[v].scale);
     for (int v : colv) push_u(vec_in, v);
     for (int v : rowv) push_u(vec_in, v);
-    StreamGeom geo = stream_geometry(M, N, E);
+    StreamGeom geo = stream_geometry(s, calls, E);
     if (gemv_calls.size() * (size_t)(geo.W / geo.CWV) * geo.G * ((N + 64L * E - 1) / (64L * E)) * 4 > 32 * 1024) geo.CWV = 1;
     const int W = geo.W, G = geo.G, U = geo.U, CWV = geo.CWV, T = W / CWV, NT = 64 * W;
     kc.geom.k = 1;
@@ -1044,8 +1061,14 @@ static KernelCode gen_mat_stream(const Script& s, const std::vector<int>& calls,
 // most 256 columns go four to a wave (200000 x 60 23 us, 41 one by one). 16-byte
 // units of BF16 and FP8 read two to four times their own bytes of x, which two
 // or four rows share (gemv of FP8 16384 x 16384: 52 us with four rows, 66 with
-// two).
-static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E) {
+// two). Rows are shared by as many as the registers allow: units of U strips of G rows as
+// they lie in memory (row_regs a row and strip) and of the column vectors (cols_regs) stay
+// within kStreamBudget, half of a lane's 256 VGPRs, as decoded values take the rest. Four
+// FP8 matrices of 16384 x 16384 165 us with two rows a wave, 187 with four; FP8 + FP8 +
+// three of FP32 925 with one, 1196 (90 VGPRs spilled) with four. The order of a row's sum
+// does not depend on G.
+constexpr int kStreamBudget = 128;
+static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E, int row_regs, int cols_regs) {
     StreamGeom g{4, 1, 1, 1};
     const int64_t ch = (cols + 64 * E - 1) / (64 * E);   // strips of a row
     int64_t pch = 1;
@@ -1062,6 +1085,7 @@ static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E) {
     if (E > 4) {
         g.U = ch == 1 ? 1 : 2;
         g.G = rows >= 1024 ? (ch >= 16 ? 4 : 2) : 1;
+        while (g.G > 1 && g.U * (g.G * row_regs + cols_regs) > kStreamBudget) g.G /= 2;
         return g;
     }
     g.U = (int)std::min<int64_t>(full, std::max<int64_t>(1, pch / g.CWV));
