@@ -129,8 +129,14 @@ void kernel_bytes(const Script& s, const std::vector<int>& calls, const std::vec
 // Waves that split the row blocks: four lane groups each, so that a group's share
 // is about one round of eight loads (80 blocks of 9811 columns with sixteen waves 4.9 us,
 // more merging than adding, with four 3.8; 256 of 1021 columns with sixteen 4.6, with
-// eight 3.9).
-static int finish_waves(long NB) { return NB > 128 ? 8 : 4; }
+// eight 3.9). Up to eight blocks are one round of loads of a single lane, which then
+// adds them without lane groups, LDS or a barrier (whole plans: BiCGK n = 64 7.7 us, 8.3
+// with four waves; column-major GESUMMV n = 40 8.0, 9.3). At 32 blocks the waves are worth
+// it (BiCGK n = 1024 8.8 us, 11.3 alone).
+constexpr int kFinishFew = 8;
+static bool finish_alone(long NB, bool dyn) { return NB <= kFinishFew && !dyn; }
+static int finish_waves(long NB, bool dyn) { return finish_alone(NB, dyn) ? 1 : NB > 128 ? 8 : 4; }
+static int finish_cols(long NB, bool dyn) { return finish_alone(NB, dyn) ? 64 : kFinishCols; }
 
 // Chains in which the partial sums of a row are added before they are merged: as many
 // as a wave that streams a row has strips in flight, so that strip and row-stream kernels
@@ -139,7 +145,7 @@ static int row_chains(int E) { return E == 4 ? 8 : 2; }
 
 // Finishing launch of column partials (both BLAS-2 schedules): a workgroup takes
 // FC float4 columns, and the 64 / FC lane groups of its FW waves split the row
-// blocks. Group gid adds blocks gid, gid + FWG, ... of each gemtv call's partials at
+// blocks (all of them one lane's where they are few, `alone`). Group gid adds blocks gid, gid + FWG, ... of each gemtv call's partials at
 // columns cc .. cc + 3, compensated; the groups of a wave and then the waves (in
 // wave order, through LDS, one buffer reused call by call) are merged as pairs,
 // and lanes below FC of wave 0 end with sum<c>. Expects lane, wave, cc, N, NB, NP,
@@ -148,10 +154,10 @@ static int row_chains(int E) { return E == 4 ? 8 : 2; }
 // workgroup give four times the workgroups of 64 and a quarter of the loads
 // per lane (ATAX 30011 x 1021: that launch 6.3 -> 3.9 us).
 static void emit_colpart_finish(Emitter& f, const std::vector<int>& gemtv_calls,
-                                const std::map<int, size_t>& ws_off) {
-    f.l("__shared__ kf_f4 kf_fr[2][FW][FC];");
+                                const std::map<int, size_t>& ws_off, bool alone) {
+    if (!alone) f.l("__shared__ kf_f4 kf_fr[2][FW][FC];");
     f.l("constexpr int FWG = FW * (64 / FC);");
-    f.l("const int gid = wave * (64 / FC) + lane / FC;");
+    f.l(alone ? "constexpr int gid = 0;" : "const int gid = wave * (64 / FC) + lane / FC;");
     bool first = true;
     for (int c : gemtv_calls) {
         const size_t off = ws_off.at(c);
@@ -165,6 +171,10 @@ static void emit_colpart_finish(Emitter& f, const std::vector<int>& gemtv_calls,
         f.l(F("    for (int i = 0; i < 8; ++i) if (b0 + (long)i * FWG < NB) pc%d = kf_cs4_add(pc%d, pv[i]);", c, c));
         f.l("  }");
         f.l("}");
+        if (alone) {
+            f.l(F("const kf_f4 sum%d = kf_cs4_value(pc%d);", c, c));
+            continue;
+        }
         f.l(F("for (int m = 32; m >= FC; m >>= 1) pc%d = kf_cs4_merge(pc%d, kf_cs4_down(pc%d, m));", c, c, c));
         if (!first) f.l("__syncthreads();");
         first = false;
@@ -610,9 +620,9 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         }
         finl.args.push_back({ArgKind::Workspace, -1});
         fsig.push_back("const float* __restrict__ ws");
-        const int FW = finish_waves(NB), FWb = col_part ? 64 * FW : 256;
+        const int FW = finish_waves(NB, p.dyn), FC = finish_cols(NB, p.dyn), FWb = col_part ? 64 * FW : 256;
         const long RBK = row_part ? (M + FWb - 1) / FWb : 0;
-        const long CBK = col_part ? (NP / 4 + kFinishCols - 1) / kFinishCols : 0;
+        const long CBK = col_part ? (NP / 4 + FC - 1) / FC : 0;
         if (p.dyn) {
             finl.args.push_back({ArgKind::ShapeM, -1});
             finl.args.push_back({ArgKind::ShapeN, -1});
@@ -625,7 +635,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         } else {
             f.l(F("constexpr long M = %ldL, N = %ldL, SR = %ldL, NB = %ldL, NP = %ldL, RBK = %ldL;", M, N, SR, NB, NP, RBK));
         }
-        f.l(F("constexpr int FW = %d, FC = %d; (void)FW; (void)FC;", FW, kFinishCols));
+        f.l(F("constexpr int FW = %d, FC = %d; (void)FW; (void)FC;", FW, FC));
         for (int v : scalars) {
             if (s.values[v].kind == VK::Const) f.l(F("const float %s = P%d;", scal_name(v).c_str(), v));
             else f.l(F("const float %s = *P%d;", scal_name(v).c_str(), v));
@@ -661,7 +671,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
             f.ind++;
             f.l("const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;");
             f.l("const long cc = 4L * ((long)(blockIdx.x - RBK) * FC + lane % FC);");
-            emit_colpart_finish(f, gemtv_calls, ws_off);
+            emit_colpart_finish(f, gemtv_calls, ws_off, finish_alone(NB, p.dyn));
             f.l("if (wave == 0 && lane < FC && cc < N) {");
             f.ind++;
             for (int c : gemtv_calls) {
@@ -1746,11 +1756,11 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         for (int v : scalars)
             f.l(s.values[v].kind == VK::Const ? F("const float %s = P%d;", scal_name(v).c_str(), v)
                                               : F("const float %s = *P%d;", scal_name(v).c_str(), v));
-        const int FW = finish_waves(NB);
-        f.l(F("constexpr int FW = %d, FC = %d;", FW, kFinishCols));
+        const int FW = finish_waves(NB, false), FC = finish_cols(NB, false);
+        f.l(F("constexpr int FW = %d, FC = %d;", FW, FC));
         f.l("const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;");
         f.l("const long cc = 4L * ((long)blockIdx.x * FC + lane % FC);");
-        emit_colpart_finish(f, gemtv_calls, ws_off);
+        emit_colpart_finish(f, gemtv_calls, ws_off, finish_alone(NB, false));
         f.l("if (wave == 0 && lane < FC && cc < N) {");
         f.ind++;
         for (size_t i = 0; i < gemtv_calls.size(); ++i) {
@@ -1768,7 +1778,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         }
         f.ind--;
         f.l("}");
-        finl.grid = (int)((NP / 4 + kFinishCols - 1) / kFinishCols);
+        finl.grid = (int)((NP / 4 + FC - 1) / FC);
         finl.block = 64 * FW;
     }
     std::string sigs, fsigs;

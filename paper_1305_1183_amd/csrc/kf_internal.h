@@ -120,7 +120,7 @@ enum class ArgKind : int {
 };
 struct KArg { ArgKind kind; int value; };   // value id (or -1 for the workspace)
 
-// float4 columns per workgroup of a finishing launch
+// float4 columns per workgroup of a finishing launch (of more than a few row blocks)
 constexpr int kFinishCols = 16;
 
 // One HIP kernel launch: the main pass of a plan kernel, or the pass that
