@@ -329,9 +329,11 @@ MatParams default_mat_params(int64_t rows, int64_t cols, const MatParams& req, i
 //    1 KiB boundaries take two float4 per lane, as strip edges then cost part of a
 //    line on each side: n = 9000 131 (one float4: 163). Rows of fewer than 256 columns
 //    fill part of a strip and want sixteen waves a CU: 89702 x 100 32 (eight: 44); so do
-//    BF16 and FP8 sources, which read less than they store: BF16 n = 4000 28 (32).
-//    Without column sums there are no partials to save, and narrow matrices keep the
-//    small workgroups: ger 89702 x 100 23 (40), 20000 x 700 29 (31), 9000 163 (128).
+//    BF16 and FP8 sources, which read less than they store, up to 400M elements: BF16 n =
+//    4000 28 (32), 6000 x 30000 247 (273), 24000 x 20100 803 (646). Without column sums
+//    there are no partials to save, and narrow matrices keep the small workgroups: ger
+//    89702 x 100 23 (40), 20000 x 700 29 (31), 9000 163 (128); BF16 and FP8 up to 40M
+//    elements: BF16 2000 x 8000 21 (27), 6000 53 (56), 9000 133 (124).
 //  - other FP32 kernels: one workgroup of sixteen waves per CU, 2 KiB strips. BiCGK
 //    n = 16384 165 (2048 workgroups of four waves: 186), 5003 21.3 (26.5), 12001 94
 //    (124), 700 x 16000 12.5 (22.6).
@@ -361,10 +363,12 @@ static MatParams library_mat_params(int64_t rows, int64_t cols, int E, bool stor
     const int64_t few = default_mat_params(rows, cols, MatParams(), E).rows, chain = few / 4;
     const int64_t by_row = chain + chain / 16, by_step = (11 * chain - 17) / 5;   // rows of a wave, within 5% of its error
     int per_cu;
-    const bool small = (double)rows * (double)cols <= 6e6, general = !small && !stores;
+    const double elems = (double)rows * (double)cols;
+    const bool small = elems <= 6e6, general = !small && !stores, ragged = quantized && cols % 256 != 0;
     if (small) { p.k = 1; p.waves = 8; p.group = 4; per_cu = 16; }
-    else if (stores && !column_sums && cols < 1024) return default_mat_params(rows, cols, p, E);
-    else if (stores && (cols < 256 || (quantized && cols % 256 != 0))) { p.k = 1; p.waves = 8; p.group = 4; per_cu = 16; }
+    else if (stores && !column_sums && (cols < 1024 || (ragged && elems <= 4e7)))
+        return default_mat_params(rows, cols, p, E);
+    else if (stores && (cols < 256 || (ragged && column_sums && elems <= 4e8))) { p.k = 1; p.waves = 8; p.group = 4; per_cu = 16; }
     else if (stores) { const bool line = cols % 256 == 0; p.k = line ? 1 : 2; p.waves = 8; p.group = line ? 4 : 2; per_cu = 8; }
     else if (E == 4) { p.k = 2; p.waves = 16; p.group = 1; per_cu = 16; }
     else if (cols <= 2 * 64 * E) { p.k = 1; p.waves = 16; p.group = 2; per_cu = 16; }

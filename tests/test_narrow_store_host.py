@@ -1,6 +1,7 @@
-"""Kernels that store a matrix of few columns keep enough waves on the chip: rank-one
-updates alone take small workgroups below 1024 columns, GEMVER's first kernel sixteen
-waves a CU below 256 and for BF16 and FP8 sources off 1 KiB boundaries."""
+"""Kernels that store a matrix keep enough waves on the chip where it has few columns or
+is quantised: rank-one updates alone take small workgroups below 1024 columns and for
+BF16 and FP8 sources off 1 KiB boundaries, GEMVER's first kernel sixteen waves a CU
+below 256 and for such sources."""
 import json
 
 import pytest
@@ -41,3 +42,13 @@ def test_quantised_source_off_line_boundaries(dtype, m, n):
     kf.kf_plan_destroy(p)
     assert k["params"]["k"] == 1
     assert k["launches"][0]["grid"] * k["launches"][0]["block"] >= 256 * 14 * 64, k
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("m,n,small", [(4001, 4000, True), (2000, 8000, True), (9001, 9000, False), (4096, 4096, False)])
+def test_quantised_rank_one_update_alone(dtype, m, n, small):
+    q = S.gemver_q(m, n, 1.5, 0.75, dtype)
+    p = kf.kf_compile(q.script, mode="unfused", flags=CG)
+    k = json.loads(kf.kf_plan_describe(p))["kernels"][0]["params"]
+    kf.kf_plan_destroy(p)
+    assert (k["waves"] == 4) == small, k
