@@ -407,7 +407,8 @@ kf_status kf_time_plan_kernels(kf_plan* p, void* stream, int32_t warmup, int32_t
  * row-resident and row-stream kernels report what was requested, 0 for the
  * library's own geometry;
  * mat_unit as requested, and only for kernels that load a BF16 or FP8
- * matrix). */
+ * matrix). Compiling the kernel again with the reported values gives the same
+ * kernel. */
 kf_status kf_plan_kernel_params(const kf_plan* p, int32_t k, kf_impl_params* out);
 
 /* ---- introspection -------------------------------------------------------- */

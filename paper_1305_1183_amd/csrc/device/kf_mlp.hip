@@ -256,7 +256,8 @@ __global__ void __launch_bounds__(MLP_NT) mlp_rows_kernel(mlp_net m) {
     }
 }
 
-// h = 32 C, C <= 4, and d a multiple of 32: one tile per wave, no masks. Every
+// h = 32 C for C = 1, 2, 4 (32, 64 and 128, the widths of the cost models; 96 goes the
+// general way, for no other reason), and d a multiple of 32: one tile per wave, no masks. Every
 // layer waits for the one before, so what counts is the latency of its weights:
 // the slices a wave multiplies (hidden layers 1 .. L - 1 forward, then L - 1 .. 1
 // backward) are loaded two layers ahead, and what the output layer reads at the
