@@ -175,9 +175,9 @@ __device__ __forceinline__ float kf_dotk(const kf_f4* a, const kf_f4* b) {
 // exchanges waits for the LDS pipe at every link instead (about 100 cycles
 // each, once per row group). Each lane adds the same pairs as a bpermute
 // butterfly would, so the results do not change by a bit. Measured against the
-// bpermute chain (whole plans): single-pass ATAX 30011 x 1021 85.3 -> 78.3 us,
-// BiCGK n = 1024 9.2 -> 8.3 us, GESUMMV n = 5003 47.4 -> 46.5 us, BiCGK
-// n = 16384 181.4 -> 180.0 us.
+// bpermute chain (whole plans): single-pass ATAX 30011 x 1021 33.2 -> 25.2 us, FP8 BiCGK
+// n = 16384 68.6 -> 54.7, GESUMMV n = 5003 33.1 -> 31.8, BiCGK n = 1024 8.9 both.
+// Strip kernels over large FP32 matrices are the exception and keep the chain.
 //
 // The values of the two lanes l and l ^ MASK (MASK 32 or 16) as (x, y): of a
 // where bit MASK of l is clear and of b where it is set, the lower lane's first.
@@ -248,6 +248,34 @@ __device__ __forceinline__ float kf_rows_reduce_from(float* v) {
 template <int LG>
 __device__ __forceinline__ float kf_rows_reduce(float* v) {
     return kf_rows_reduce_from<32, (1 << LG)>(v);
+}
+// The same sums through ds_bpermute: the same pairs, so the same bits.
+template <int MASK>
+__device__ __forceinline__ float kf_lds_xor(float v) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute((int)((__lane_id() ^ MASK) << 2), __float_as_int(v)));
+}
+template <int MASK, int G>
+__device__ __forceinline__ float kf_rows_reduce_lds_from(float* v) {
+    if constexpr (G == 1) {
+        if constexpr (MASK > 0) {
+            v[0] += kf_lds_xor<MASK>(v[0]);
+            return kf_rows_reduce_lds_from<MASK / 2, 1>(v);
+        } else return v[0];
+    } else {
+        constexpr int half = G / 2;
+        const bool hi = (__lane_id() & MASK) != 0;
+#pragma unroll
+        for (int j = 0; j < half; ++j) {
+            const float send = hi ? v[j] : v[j + half];
+            const float keep = hi ? v[j + half] : v[j];
+            v[j] = keep + kf_lds_xor<MASK>(send);
+        }
+        return kf_rows_reduce_lds_from<MASK / 2, half>(v);
+    }
+}
+template <int LG>
+__device__ __forceinline__ float kf_rows_reduce_lds(float* v) {
+    return kf_rows_reduce_lds_from<32, (1 << LG)>(v);
 }
 
 // ---- B6: workgroup sum in wave order -----------------------------------------

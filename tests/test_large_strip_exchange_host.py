@@ -1,0 +1,20 @@
+"""Row sums of strip kernels over more than 200M FP32 elements exchange through LDS, in
+the library's geometry and in requested ones; other kernels stay in the vector ALU."""
+import pytest
+
+from paper_1305_1183_amd import kf
+from paper_1305_1183_amd import sequences as S
+
+POINT = dict(mat_k=1, mat_waves=4, mat_group=2, mat_rows=1024)
+
+
+@pytest.mark.parametrize("m,n,fmt,point,lds", [
+    (16384, 16384, "f32", {}, True), (16384, 16384, "f32", POINT, True), (14143, 14143, "f32", POINT, True),
+    (14142, 14142, "f32", POINT, False), (4096, 4096, "f32", {}, False), (32768, 32768, "bf16", {}, False),
+    (32768, 32768, "fp8", POINT, False)])
+def test_exchange(m, n, fmt, point, lds):
+    q = S.bicgk_q(m, n, fmt)
+    p = kf.kf_compile(q.script, mode="fused", flags=kf.KF_COMPILE_CODEGEN_ONLY, **point)
+    src = kf.kf_plan_source(p, 0)
+    kf.kf_plan_destroy(p)
+    assert ("kf_rows_reduce_lds<" in src) == lds and ("kf_rows_reduce<" in src) != lds
