@@ -154,7 +154,7 @@ static int row_chains(int E) { return E == 4 ? 8 : 2; }
 // workgroup give four times the workgroups of 64 and a quarter of the loads
 // per lane (ATAX 30011 x 1021: that launch 6.3 -> 3.9 us).
 static void emit_colpart_finish(Emitter& f, const std::vector<int>& gemtv_calls,
-                                const std::map<int, size_t>& ws_off, bool alone) {
+                                const std::map<int, size_t>& ws_off, bool alone, bool pair_parts) {
     if (!alone) f.l("__shared__ kf_f4 kf_fr[2][FW][FC];");
     f.l("constexpr int FWG = FW * (64 / FC);");
     f.l(alone ? "constexpr int gid = 0;" : "const int gid = wave * (64 / FC) + lane / FC;");
@@ -166,9 +166,15 @@ static void emit_colpart_finish(Emitter& f, const std::vector<int>& gemtv_calls,
         f.l(F("kf_cs4 pc%d = kf_cs4_init(kf_zero4());", c));
         f.l("if (cc < N) {");
         f.l("  for (long b0 = gid; b0 < NB; b0 += 8 * FWG) {");
-        f.l("    kf_f4 pv[8];");
-        f.l(F("    for (int i = 0; i < 8; ++i) { const long b = b0 + (long)i * FWG; pv[i] = b < NB ? kf_ld4(ws + %zuL + b * NP + cc) : kf_zero4(); }", off));
-        f.l(F("    for (int i = 0; i < 8; ++i) if (b0 + (long)i * FWG < NB) pc%d = kf_cs4_add(pc%d, pv[i]);", c, c));
+        if (pair_parts) {   // the errors follow the sums of all blocks
+            f.l("    kf_cs4 pv[8];");
+            f.l(F("    for (int i = 0; i < 8; ++i) { const long b = b0 + (long)i * FWG; const float* at = ws + %zuL + b * NP + cc; pv[i] = kf_cs4_init(kf_zero4()); if (b < NB) { pv[i].s = kf_ld4(at); pv[i].c = kf_ld4(at + NB * NP); } }", off));
+            f.l(F("    for (int i = 0; i < 8; ++i) if (b0 + (long)i * FWG < NB) pc%d = kf_cs4_merge(pc%d, pv[i]);", c, c));
+        } else {
+            f.l("    kf_f4 pv[8];");
+            f.l(F("    for (int i = 0; i < 8; ++i) { const long b = b0 + (long)i * FWG; pv[i] = b < NB ? kf_ld4(ws + %zuL + b * NP + cc) : kf_zero4(); }", off));
+            f.l(F("    for (int i = 0; i < 8; ++i) if (b0 + (long)i * FWG < NB) pc%d = kf_cs4_add(pc%d, pv[i]);", c, c));
+        }
         f.l("  }");
         f.l("}");
         if (alone) {
@@ -676,7 +682,7 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
             f.ind++;
             f.l("const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;");
             f.l("const long cc = 4L * ((long)(blockIdx.x - RBK) * FC + lane % FC);");
-            emit_colpart_finish(f, gemtv_calls, ws_off, finish_alone(NB, p.dyn));
+            emit_colpart_finish(f, gemtv_calls, ws_off, finish_alone(NB, p.dyn), false);
             f.l("if (wave == 0 && lane < FC && cc < N) {");
             f.ind++;
             for (int c : gemtv_calls) {
@@ -1513,10 +1519,18 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         return F("cv%d[j]", v);
     };
     const bool col_part = !gemtv_calls.empty() && NB > 1;
+    // A team's chain of column sums is shorter than the R rows of a workgroup that shares its
+    // rows, but the teams' total is rounded once more. Where the one does not make up for
+    // the other (up to 1024 rows), the total goes to the finishing launch as a pair, and
+    // there are still fewer partials than in the wide geometry: ATAX 1024 x 1024 relative
+    // error 7.0e-8 (7.3e-8 with one FP32 total a block) and 9.0 us (8.9), 500 x 500 7.1e-8
+    // (7.4e-8) and 8.9 us (8.8).
+    const RowresGeom wide = rowres_geometry(M, N, MatParams());
+    const bool pair_parts = T > 1 && col_part && (R + T - 1) / T + 2 > wide.R && 2 * NB <= (M + wide.R - 1) / wide.R;
     std::map<int, size_t> ws_off;
     size_t wsz = 0;
     if (col_part)
-        for (int c : gemtv_calls) { ws_off[c] = wsz; wsz += (size_t)NB * NP; }
+        for (int c : gemtv_calls) { ws_off[c] = wsz; wsz += (size_t)(pair_parts ? 2 * NB : NB) * NP; }
     kc.ws_floats = wsz;
 
     std::vector<int> main_out;
@@ -1708,7 +1722,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
                 const int c = gemtv_calls[i];
                 e.l(F("kf_cs4 cs%d = kf_cs4_init(kf_red[%zu][0][q]);", c, i));
                 e.l(F("for (int t = 1; t < T; ++t) cs%d = kf_cs4_add(cs%d, kf_red[%zu][t][q]);", c, c, i));
-                e.l(F("const kf_f4 csum%d = kf_cs4_value(cs%d);", c, c));
+                if (!pair_parts) e.l(F("const kf_f4 csum%d = kf_cs4_value(cs%d);", c, c));
             }
             e.l("const long cc = 4L * q;");
         } else {
@@ -1728,6 +1742,8 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
                 e.l(F("const kf_f4 g%d = %s;", c, val.c_str()));
                 if (must_store(s, part, kid, k.out)) e.l(F("kf_st4_tail(Y%d, cc, N, g%d);", k.out, c));
                 else e.l(F("(void)g%d;", c));
+            } else if (pair_parts) {
+                e.l(F("kf_st4(ws + %zuL + rb * NP + cc, cs%d.s); kf_st4(ws + %zuL + (%ldL + rb) * NP + cc, cs%d.c);", ws_off[c], c, ws_off[c], NB, c));
             } else {
                 e.l(F("kf_st4(ws + %zuL + rb * NP + cc, %s);", ws_off[c], (T > 1 ? F("csum%d", c) : F("acc%d[j]", c)).c_str()));
             }
@@ -1765,7 +1781,7 @@ static KernelCode gen_mat_rowres(const Script& s, const std::vector<int>& calls,
         f.l(F("constexpr int FW = %d, FC = %d;", FW, FC));
         f.l("const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;");
         f.l("const long cc = 4L * ((long)blockIdx.x * FC + lane % FC);");
-        emit_colpart_finish(f, gemtv_calls, ws_off, finish_alone(NB, false));
+        emit_colpart_finish(f, gemtv_calls, ws_off, finish_alone(NB, false), pair_parts);
         f.l("if (wave == 0 && lane < FC && cc < N) {");
         f.ind++;
         for (size_t i = 0; i < gemtv_calls.size(); ++i) {
