@@ -503,8 +503,9 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
             // FP32 strips of more than 200M elements exchange through LDS, whose latency the
             // stream hides: BiCGK n = 16384 164 us (169 by DPP; four waves, two rows a step and
             // 1024 rows 159, 162; one row a step and 256 rows 181, 189), 32768 673 (688), 14500
-            // 137 (139), 12001 95.1 both, 4096 16.9 (16.5). BF16 n = 32768 421 (337).
-            const char* lds = E == 4 && (double)M * (double)N > 2e8 ? "_lds" : "";
+            // 137 (139), 12001 95.1 both, 4096 16.9 (16.5). BF16 n = 32768 421 (337); in units of
+            // four elements 343 (325), FP8 321 (289).
+            const char* lds = !kernel_has_quantized(s, calls) && (double)M * (double)N > 2e8 ? "_lds" : "";
             for (int c : gemv_calls) e.l(F("const float sum%d = kf_rows_reduce%s<LG>(rp%d);", c, lds, c));
             e.l("{");
             e.ind++;

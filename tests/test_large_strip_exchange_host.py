@@ -11,7 +11,8 @@ POINT = dict(mat_k=1, mat_waves=4, mat_group=2, mat_rows=1024)
 @pytest.mark.parametrize("m,n,fmt,point,lds", [
     (16384, 16384, "f32", {}, True), (16384, 16384, "f32", POINT, True), (14143, 14143, "f32", POINT, True),
     (14142, 14142, "f32", POINT, False), (4096, 4096, "f32", {}, False), (32768, 32768, "bf16", {}, False),
-    (32768, 32768, "fp8", POINT, False)])
+    (32768, 32768, "fp8", POINT, False), (32768, 32768, "fp8", dict(POINT, mat_unit=4), False),
+    (32768, 32768, "bf16", dict(mat_unit=4), False)])
 def test_exchange(m, n, fmt, point, lds):
     q = S.bicgk_q(m, n, fmt)
     p = kf.kf_compile(q.script, mode="fused", flags=kf.KF_COMPILE_CODEGEN_ONLY, **point)
