@@ -340,7 +340,9 @@ MatParams default_mat_params(int64_t rows, int64_t cols, const MatParams& req, i
 //  - BF16 and FP8 in 16-byte units: 24 and 20 waves per CU, as many as their registers
 //    allow, hide the conversion. BiCGK n = 16384 FP8 54 (79), BF16 90 (96). One or two
 //    strips leave row blocks only; sixteen waves a workgroup then keep their number down
-//    (FP8 50000 x 500 21, 50).
+//    (FP8 50000 x 500 21, 50). In requested units of four elements, which carry a quarter
+//    or half of the bytes, 24 waves of two rows from 40M elements on: FP8 n = 16384 60 (the
+//    line before 95, small workgroups 77), n = 8192 22 (30, 24), 5003 18.4 (16.9, 20).
 // The number of workgroups stays within one round of the chip: a few more would run in
 // a second, nearly empty one (BiCGK n = 10007 98 with 260 workgroups, 66 with 240; n =
 // 24000 493 with 282, 354 with 235).
@@ -370,6 +372,7 @@ static MatParams library_mat_params(int64_t rows, int64_t cols, int E, bool stor
         return default_mat_params(rows, cols, p, E);
     else if (stores && (cols < 256 || (ragged && column_sums && elems <= 4e8))) { p.k = 1; p.waves = 8; p.group = 4; per_cu = 16; }
     else if (stores) { const bool line = cols % 256 == 0; p.k = line ? 1 : 2; p.waves = 8; p.group = line ? 4 : 2; per_cu = 8; }
+    else if (E == 4 && quantized && elems > 4e7) { p.k = 2; p.waves = 8; p.group = 2; per_cu = 24; }
     else if (E == 4) { p.k = 2; p.waves = 16; p.group = 1; per_cu = 16; }
     else if (cols <= 2 * 64 * E) { p.k = 1; p.waves = 16; p.group = 2; per_cu = 16; }
     else { p.k = 1; p.waves = 4; p.group = 2; per_cu = E == 16 ? 20 : 24; }
