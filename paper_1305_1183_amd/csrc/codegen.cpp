@@ -797,9 +797,15 @@ static bool is_stream(const Script& s, const std::vector<int>& calls, const MatP
     std::set<int> mats, cols;
     stream_operands(s, calls, &mats, &cols);
     if (!gemv || mats.size() + cols.size() > 6) return false;
-    // a launch has fewer than 2^32 threads: past that, strips of many rows a workgroup
     const Space sp = call_space(s, calls[0]);
-    const StreamGeom g = stream_geometry(s, calls, kernel_unit_elems(s, calls, p.unit));
+    const int E = kernel_unit_elems(s, calls, p.unit);
+    // One BF16 or FP8 matrix of few long rows leaves too few waves that each walk many
+    // strips: column strips and a finishing launch are faster (FP8 1500 x 20000 11.9 us,
+    // streamed 16.5; 2500 x 25000 20.0, 27.9; 4000 x 20000 22.0, 23.1; 4096 x 16384 18.0, 15.8;
+    // BF16 1100 x 30000 18.0, 21.8; 1500 x 9000 11.1, 9.7; 2048 x 16384 15.7, 14.2)
+    if (E > 4 && mats.size() == 1 && sp.b >= 16384 && sp.a >= 1024 && sp.a < (E == 16 ? 4096 : 1500)) return false;
+    // a launch has fewer than 2^32 threads: past that, strips of many rows a workgroup
+    const StreamGeom g = stream_geometry(s, calls, E);
     const int64_t per = (int64_t)(g.W / g.CWV) * g.G;
     return (sp.a + per - 1) / per * g.W * 64 < ((int64_t)1 << 32);
 }
@@ -1108,10 +1114,14 @@ static StreamGeom stream_geometry(int64_t rows, int64_t cols, int E, int row_reg
         g.U = ch == 1 ? 1 : 2;
         g.G = rows >= 1024 ? (ch >= 16 ? 4 : 2) : 1;
         while (g.G > 1 && g.U * (g.G * row_regs + cols_regs) > kStreamBudget) g.G /= 2;
+        while (g.G > 1 && rows / g.G * g.CWV < 1024) g.G /= 2;   // BF16 2000 x 8000 8.9 us, 12.4 without
         return g;
     }
     g.U = (int)std::min<int64_t>(full, std::max<int64_t>(1, pch / g.CWV));
     if (g.U == 1 && g.CWV == 1 && rows >= 4096) g.G = 4;   // rows of at most 256 columns
+    // units of four BF16 or FP8 elements are a half or a quarter of FP32's bytes: two rows a
+    // wave on large matrices (FP8 n = 16384 62 us, 82 with one; 2000 x 8000 9.2, 7.6)
+    if (row_regs < 4 && (double)rows * (double)cols > 3.2e7) g.G = std::max(g.G, 2);
     return g;
 }
 
