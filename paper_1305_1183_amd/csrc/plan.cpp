@@ -395,6 +395,9 @@ static MatParams library_mat_params(int64_t rows, int64_t cols, int E, bool stor
     } else if (p.group == 1) {
         most = std::min(most, by_row * p.waves);
     } else if (wave_rows() > chain) {
+        // a lane of sixteen FP8 columns has no registers for pairs beside the stored matrix
+        // (GEMVER's first kernel at n = 16384 1314 us, small workgroups 995)
+        if (stores && E == 16) return default_mat_params(rows, cols, MatParams(), E);
         p.sums = ColSum::Pairs;
     }
     if (r > most) {
