@@ -384,9 +384,11 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
         // are loaded before the first is decoded. From four on the compiler has to be
         // told: it puts a decode, and the wait for its unit, between them (BiCGK of FP8
         // 32768 x 32768, two units a lane and two rows a step: 329 us so, 237 in order;
-        // steps of two units 0 to 4% slower in order).
+        // steps of two units 0 to 4% slower in order). Kernels that store a matrix decode each
+        // unit as it comes, which spreads their stores (GEMVER of BF16 in wide units, four
+        // rows a step, n = 32768 2650 us, 3049 in order).
         for (int v : mat_in) e.l(F("kf_f4 L%d[G][K];", v));
-        auto units = [&](int v) { return s.values[v].dtype != KF_F32 && E > 4 ? U * (E * dtype_size(s.values[v].dtype) / 16) : 0; };
+        auto units = [&](int v) { return mat_out.empty() && s.values[v].dtype != KF_F32 && E > 4 ? U * (E * dtype_size(s.values[v].dtype) / 16) : 0; };
         for (int v : mat_in)
             if (!edge && units(v)) e.l(F("kf_u4 Q%d[G][%d];", v, units(v)));
         e.l("#pragma unroll");
@@ -413,7 +415,9 @@ static KernelCode gen_mat(const Script& s, const std::vector<int>& calls,
                 e.l(F("for (int u = 0; u < %d; ++u) {", U * (E / per)));
                 e.ind++;
                 e.l(F("const long cu0 = col[(u / %d) * EG] + (long)(u %% %d) * %d;", E / per, E / per, per));
-                if (!edge) {
+                if (!edge && !mat_out.empty()) {
+                    e.l(F("%s(kf_ldu_nt(M%d + (row * LD%d + cu0) * %d), &L%d[gi][u * %d]);", dec, v, v, es, v, EQ));
+                } else if (!edge) {
                     e.l(F("Q%d[gi][u] = kf_ldu_nt(M%d + (row * LD%d + cu0) * %d);", v, v, v, es));
                 } else {
                     e.l(F("if (row < r1 && cu0 < N) { %s(kf_ldu_nt(M%d + (row * LD%d + cu0) * %d), &L%d[gi][u * %d]);", dec, v, v, es, v, EQ));
@@ -1363,7 +1367,7 @@ bool needs_rowres(const Script& s, const std::vector<int>& calls) {
 // end. One workgroup per CU as in the wide geometry, so no more partials; short
 // matrices keep four rows per team. Single-pass ATAX, whole plans: 30011 x 1021
 // 82 us -> 25 us, 20000 x 1500 40 -> 25, 32768 x 256 30 -> 11 (four rows per group; one
-// row per group 24), 1024 x 1024 12.3 -> 9.3. Of these 0 to 4% are the pairs in which the
+// row per group 24), 1024 x 1024 12.4 -> 9.1. Of these 0 to 4% are the pairs in which the
 // 256-column parts of a row dot meet, as they do where waves share a row.
 static RowresGeom rowres_team_geometry(int64_t rows, int64_t cols) {
     RowresGeom g;

@@ -19,3 +19,12 @@ def kernels(q, mode, **opts):
 def test_stored_matrix_in_wide_units(fmt, n, small):
     p = kernels(S.gemver_q(n, n, 1.5, 0.75, fmt), "fused", mat_unit=16)[0]
     assert (p["waves"] == 4) == small, p
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp8"])
+def test_units_of_a_stored_matrix_are_decoded_as_they_come(fmt):
+    q = S.gemver_q(32768, 32768, 1.5, 0.75, fmt)
+    p = kf.kf_compile(q.script, mode="fused", flags=kf.KF_COMPILE_CODEGEN_ONLY, mat_k=1, mat_waves=8, mat_group=4, mat_rows=256, mat_unit=16)
+    src = kf.kf_plan_source(p, 0)
+    kf.kf_plan_destroy(p)
+    assert "sched_barrier" not in src and "kf_dec_%s(kf_ldu_nt(" % fmt in src
